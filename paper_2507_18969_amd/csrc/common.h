@@ -100,6 +100,15 @@ __device__ __forceinline__ uint4 ld_global16(const void* p) {
 __device__ __forceinline__ void st_global16(void* p, uint4 x) {
   *(__attribute__((address_space(1))) u32x4*)p = __builtin_bit_cast(u32x4, x);
 }
+// Raw buffer view of global memory from `base` on (32-bit byte offsets, no
+// swizzle, no index stride; word 3 as gfx9-family GPUs take it).  A load at
+// kBufferNone is out of its range: it reads zeros and touches no memory.
+constexpr int kBufferWord3 = 0x00020000;
+constexpr uint32_t kBufferNone = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_buffer(const void* base) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, 0x7FFFFFFF, kBufferWord3);
+}
+
 // A 16-byte load issued unconditionally: where `ok` is false it reads 16
 // zero bytes kept in device memory.  With no branch around the load and no
 // select after it, the compiler counts outstanding loads exactly and needs
@@ -108,6 +117,14 @@ __device__ __forceinline__ void st_global16(void* p, uint4 x) {
 __device__ __align__(16) static const uint32_t kZero16[4] = {0u, 0u, 0u, 0u};
 __device__ __forceinline__ uint4 ld_global16_or_zero(const void* p, bool ok) {
   return ld_global16(ok ? p : (const void*)kZero16);
+}
+
+// Barrier for LDS traffic only: waits for the wave's LDS accesses, not for its
+// outstanding global loads and stores.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // p[0] + p[stride] + ... + p[(n-1) stride], added strictly in index order;

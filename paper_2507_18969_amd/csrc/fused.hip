@@ -125,10 +125,6 @@ void k_adam_frags(const StepState* st, const AdamJob* jobs, int n_jobs, int tota
 // ---------------------------------------------------------------------------
 // Row-block products
 // ---------------------------------------------------------------------------
-// Word 3 of a raw buffer resource on gfx9-family GPUs (32-bit data format,
-// no swizzle, no index stride).
-constexpr int kBufferWord3 = 0x00020000;
-
 __device__ __forceinline__ f32x4 mfma16(uint4 a, uint4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
@@ -151,10 +147,6 @@ struct MmShape {
   static constexpr int NBT = (TOT + BB - 1) / BB;
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t frag_rsrc(const uint4* base) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, 0x7FFFFFFF, kBufferWord3);
-}
-
 // First batch of a product's fragment loads, into buf[0 .. BB-1]; issued
 // ahead of the product (before the previous stage's epilogue) so that its
 // latency overlaps that work.
@@ -162,7 +154,7 @@ template <int K, int NT, int B>
 __device__ __forceinline__ void mm_first(const uint4* __restrict__ base, const int (&cb)[NT],
                                          uint4 (&buf)[B]) {
   typedef MmShape<K, NT, B> S;
-  const __amdgpu_buffer_rsrc_t rs = frag_rsrc(base);
+  const __amdgpu_buffer_rsrc_t rs = raw_buffer(base);
   const int voff = (threadIdx.x & 63) * 16;
 #pragma unroll
   for (int q = 0; q < S::BB; ++q) {
@@ -179,7 +171,7 @@ __device__ __forceinline__ void mm_rest(const bf16_t* sA, int lda, const uint4* 
   typedef MmShape<K, NT, B> S;
   constexpr int KB = S::KB, TOT = S::TOT, BB = S::BB, NBT = S::NBT;
   const int lane = threadIdx.x & 63;
-  const __amdgpu_buffer_rsrc_t rs = frag_rsrc(base);
+  const __amdgpu_buffer_rsrc_t rs = raw_buffer(base);
   const int voff = lane * 16;
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -240,14 +232,6 @@ template <int K, int NT, int B>
 __device__ __forceinline__ void mm(const bf16_t* sA, int lda, const uint4* __restrict__ base,
                                    const int (&cb)[NT], f32x4 (&acc)[NT]) {
   mm<K, NT, B>(sA, lda, base, cb, acc, [] {});
-}
-
-// Barrier for LDS traffic only: waits for the wave's LDS accesses, not for its
-// outstanding global loads and stores.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 constexpr int kFusedWaves = 8;  // waves of a row-block workgroup

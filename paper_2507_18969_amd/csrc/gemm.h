@@ -136,7 +136,12 @@ hipError_t launch_wgrad(int tile, bool bf16, const WgradProblem* d_probs, int n_
 hipError_t launch_wgrad_adam(int tile, const WgradProblem* d_probs, int n_probs, int total_tiles,
                              int elem_items, const StepState* st, const WgradAdam& ad,
                              hipStream_t s);
-// Wide tiles (gemm_wide.hip), reached through the two launchers above.
+// FP32 products (gemm_fp32.hip) and wide tiles (gemm_wide.hip), reached
+// through the launchers above.
+hipError_t launch_gemm_fp32(int tile, bool a_kmajor, bool b_kmajor, EpiKind epi, int nb,
+                            const GemmArgs& g, int grid_m_max, hipStream_t s);
+hipError_t launch_wgrad_fp32(int tile, const WgradProblem* d_probs, int n_probs, int total_tiles,
+                             const StepState* st, hipStream_t s);
 hipError_t launch_gemm_wide(int tile, bool a_kmajor, bool b_kmajor, EpiKind epi, int nb,
                             const GemmArgs& g, int grid_m_max, hipStream_t s);
 hipError_t launch_wgrad_wide(int tile, const WgradProblem* d_probs, int n_probs, int total_tiles,

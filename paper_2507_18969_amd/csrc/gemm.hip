@@ -1,5 +1,7 @@
-// MFMA matrix products for gfx950; see gemm.h for the contract.
-#include "gemm.h"
+// BF16 matrix products on 4-wave tiles (gfx950 MFMA); see gemm.h for the
+// contract, gemm_fp32.hip for the FP32 products, gemm_wide.hip for the wide
+// tiles.
+#include "gemm_epi.h"
 
 namespace edpc {
 
@@ -7,31 +9,10 @@ namespace edpc {
 // element-range Adam item (kAdamVecItem), which takes one thread an element
 constexpr int kThreads = 256;
 
-template <bool BF, int MB>
+template <int MB>
 struct Mfma;
-
 template <>
-struct Mfma<false, 32> {  // v_mfma_f32_32x32x2_f32
-  static constexpr int KSTEP = 2;
-  static constexpr int NACC = 16;
-  typedef f32x16 Acc;
-  typedef float Frag;
-  __device__ static Acc mma(Frag a, Frag b, Acc c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
-};
-template <>
-struct Mfma<false, 16> {  // v_mfma_f32_16x16x4_f32
-  static constexpr int KSTEP = 4;
-  static constexpr int NACC = 4;
-  typedef f32x4 Acc;
-  typedef float Frag;
-  __device__ static Acc mma(Frag a, Frag b, Acc c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-};
-template <>
-struct Mfma<true, 32> {  // v_mfma_f32_32x32x16_bf16
+struct Mfma<32> {  // v_mfma_f32_32x32x16_bf16
   static constexpr int KSTEP = 16;
   static constexpr int NACC = 16;
   typedef f32x16 Acc;
@@ -41,7 +22,7 @@ struct Mfma<true, 32> {  // v_mfma_f32_32x32x16_bf16
   }
 };
 template <>
-struct Mfma<true, 16> {  // v_mfma_f32_16x16x32_bf16
+struct Mfma<16> {  // v_mfma_f32_16x16x32_bf16
   static constexpr int KSTEP = 32;
   static constexpr int NACC = 4;
   typedef f32x4 Acc;
@@ -63,11 +44,10 @@ __device__ __forceinline__ int acc_col(int lane) {
 }
 
 // ---------------------------------------------------------------------------
-// Operand tile staging.  LDS layout: FP32 tiles are stored k-major
-// [BK][ROWS + 4]; BF16 tiles row-major [ROWS][BK + 8] so that one lane reads
-// its 8 consecutive k values with a single 16-byte access.  A BF16 operand
-// stored row-contiguous in memory (k slowest) is moved in 8 x 8 blocks that
-// each thread transposes in registers, so LDS still gets 16-byte stores.
+// Operand tile staging.  LDS layout: row-major [ROWS][BK + 8], so that one
+// lane reads its 8 consecutive k values with a single 16-byte access.  An
+// operand stored row-contiguous in memory (k slowest) is moved in 8 x 8 blocks
+// that each thread transposes in registers, so LDS still gets 16-byte stores.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void transpose8x8_bf16(const uint4* in, uint4* out) {
   // in[i] holds 8 bf16 of row i (columns 0..7); out[j] gets column j (rows 0..7)
@@ -100,39 +80,24 @@ __device__ __forceinline__ void blk_of(int b, int& rb, int& kb) {
   kb = 8 * v + (b & 7);
 }
 
-// FP32 tiles hold an operand k-major in LDS, [BK][ROWS + PAD].  An MFMA
-// operand read takes MB consecutive rows at each of 64 / MB k values, and
-// gfx950's LDS has 64 four-byte banks, so the read is conflict-free when the
-// row stride is MB (mod 64): the k groups land on disjoint banks.  Operands
-// staged from the row-contiguous layout are stored as 16-byte row chunks,
-// conflict-free at any stride, and take that stride.  K-major operands are
-// transposed into LDS by 4-byte stores, for which a stride of 4 (mod 64)
-// spreads a wave's stores best; they keep PAD = 4.
-constexpr int fp32_lds_pad(bool kmajor, int rows, int mb) {
-  return kmajor ? 4 : ((mb - rows % 64) % 64 + 64) % 64;
-}
-
-template <bool BF, int ROWS, int BK, int PAD = 4>
+template <int ROWS, int BK>
 struct Stage {
-  static constexpr int VEC = BF ? 8 : 4;                 // elements per 16-byte vector
+  static constexpr int VEC = 8;                          // elements per 16-byte vector
   static constexpr int NVEC = ROWS * BK / VEC;           // vectors per tile
   static constexpr int PER_THREAD = (NVEC + kThreads - 1) / kThreads;
-  static constexpr int NBLK = (ROWS / 8) * (BK / 8);     // 8 x 8 blocks (BF16, row-contiguous)
-  static_assert(!BF || (BK == 128 && ROWS % 16 == 0), "blk_of: 16 chunks, row blocks in pairs");
+  static constexpr int NBLK = (ROWS / 8) * (BK / 8);     // 8 x 8 blocks (row-contiguous)
+  static_assert(BK == 128 && ROWS % 16 == 0, "blk_of: 16 chunks, row blocks in pairs");
   static constexpr int BLK_PER_THREAD = (NBLK + kThreads - 1) / kThreads;
   static constexpr int NREG = PER_THREAD > 8 * BLK_PER_THREAD ? PER_THREAD : 8 * BLK_PER_THREAD;
-  static constexpr int STRIDE = BF ? (BK + 8) : (ROWS + PAD);  // LDS row stride (elements)
-  static constexpr int LDS_ELEMS = BF ? ROWS * (BK + 8) : BK * (ROWS + PAD);
-  static_assert(BF || (ROWS + PAD) % 4 == 0, "16-byte aligned FP32 rows");
+  static constexpr int STRIDE = BK + 8;                  // LDS row stride (elements)
+  static constexpr int LDS_ELEMS = ROWS * STRIDE;
   uint4 reg[NREG];
 
   // Global -> registers.  kmajor: src[row * ld + k]; else src[k * ld + row].
   template <bool KMAJOR>
-  __device__ __forceinline__ void load(const void* srcv, int ld, int row0, int rows_valid,
-                                       int k0, int K) {
-    const char* src = (const char*)srcv;
-    const int esz = BF ? 2 : 4;
-    if constexpr (BF && !KMAJOR) {
+  __device__ __forceinline__ void load(const bf16_t* src, int ld, int row0, int rows_valid, int k0,
+                                       int K) {
+    if constexpr (!KMAJOR) {
 #pragma unroll
       for (int p = 0; p < BLK_PER_THREAD; ++p) {
         const int b = threadIdx.x + p * kThreads;
@@ -142,33 +107,25 @@ struct Stage {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const int gk = k0 + kb * 8 + i;
-          reg[8 * p + i] = ld_global16_or_zero(src + ((long long)gk * ld + gr) * esz,
+          reg[8 * p + i] = ld_global16_or_zero(src + (long long)gk * ld + gr,
                                                b < NBLK && gr < rows_valid && gk < K);
         }
       }
-      return;
-    }
+    } else {
 #pragma unroll
-    for (int p = 0; p < PER_THREAD; ++p) {
-      const int v = threadIdx.x + p * kThreads;
-      if constexpr (KMAJOR) {
+      for (int p = 0; p < PER_THREAD; ++p) {
+        const int v = threadIdx.x + p * kThreads;
         const int row = v / (BK / VEC), kq = v % (BK / VEC);
         const int gr = row0 + row, gk = k0 + kq * VEC;
-        reg[p] = ld_global16_or_zero(src + ((long long)gr * ld + gk) * esz,
-                                     v < NVEC && gr < rows_valid && gk < K);
-      } else {
-        const int k = v / (ROWS / VEC), rq = v % (ROWS / VEC);
-        const int gr = row0 + rq * VEC, gk = k0 + k;
-        reg[p] = ld_global16_or_zero(src + ((long long)gk * ld + gr) * esz,
+        reg[p] = ld_global16_or_zero(src + (long long)gr * ld + gk,
                                      v < NVEC && gr < rows_valid && gk < K);
       }
     }
   }
 
   template <bool KMAJOR>
-  __device__ __forceinline__ void store(void* ldsv) {
-    if constexpr (BF && !KMAJOR) {
-      bf16_t* lds = (bf16_t*)ldsv;
+  __device__ __forceinline__ void store(bf16_t* lds) {
+    if constexpr (!KMAJOR) {
 #pragma unroll
       for (int p = 0; p < BLK_PER_THREAD; ++p) {
         const int b = threadIdx.x + p * kThreads;
@@ -180,25 +137,11 @@ struct Stage {
 #pragma unroll
         for (int j = 0; j < 8; ++j) *(uint4*)(lds + (rb * 8 + j) * STRIDE + kb * 8) = t[j];
       }
-      return;
-    }
+    } else {
 #pragma unroll
-    for (int p = 0; p < PER_THREAD; ++p) {
-      const int v = threadIdx.x + p * kThreads;
-      if (v >= NVEC) continue;
-      if constexpr (!BF) {
-        float* lds = (float*)ldsv;
-        const float* f = (const float*)&reg[p];
-        if constexpr (KMAJOR) {
-          const int row = v / (BK / VEC), kq = v % (BK / VEC);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) lds[(kq * 4 + j) * STRIDE + row] = f[j];
-        } else {
-          const int k = v / (ROWS / VEC), rq = v % (ROWS / VEC);
-          *(uint4*)(lds + k * STRIDE + rq * 4) = reg[p];
-        }
-      } else {
-        bf16_t* lds = (bf16_t*)ldsv;
+      for (int p = 0; p < PER_THREAD; ++p) {
+        const int v = threadIdx.x + p * kThreads;
+        if (v >= NVEC) continue;
         const int row = v / (BK / VEC), kq = v % (BK / VEC);
         *(uint4*)(lds + row * STRIDE + kq * 8) = reg[p];
       }
@@ -206,19 +149,11 @@ struct Stage {
   }
 };
 
-template <bool BF, int MB, int BK>
-__device__ __forceinline__ typename Mfma<BF, MB>::Frag frag_read(const void* ldsv, int stride,
-                                                                 int row_base, int kk, int lane) {
-  if constexpr (!BF) {
-    const float* lds = (const float*)ldsv;
-    const int r = lane % MB, k = lane / MB;
-    return lds[(kk + k) * stride + row_base + r];
-  } else {
-    const bf16_t* lds = (const bf16_t*)ldsv;
-    const int r = lane % MB, kg = lane / MB;
-    uint4 u = *(const uint4*)(lds + (row_base + r) * stride + kk + 8 * kg);
-    return __builtin_bit_cast(bf16x8, u);
-  }
+template <int MB>
+__device__ __forceinline__ bf16x8 frag_read(const bf16_t* lds, int stride, int row_base, int kk,
+                                            int lane) {
+  const int r = lane % MB, kg = lane / MB;
+  return __builtin_bit_cast(bf16x8, *(const uint4*)(lds + (row_base + r) * stride + kk + 8 * kg));
 }
 
 template <int BM_, int BN_, int MB_, int TM_, int TN_>
@@ -227,25 +162,24 @@ struct TileCfg {
 };
 
 // One output tile (m0, n0) of C = A * B_i for i < NB.
-template <bool BF, class T, bool AK, bool BKM, int NB>
+template <class T, bool AK, bool BKM, int NB>
 struct TileCompute {
-  static constexpr int BK = BF ? 128 : 64;
+  static constexpr int BK = 128;
   static constexpr int MB = T::MB, TM = T::TM, TN = T::TN;
-  typedef Mfma<BF, MB> Op;
-  typedef Stage<BF, T::BM, BK, fp32_lds_pad(AK, T::BM, T::MB)> SA;
-  typedef Stage<BF, T::BN, BK, fp32_lds_pad(BKM, T::BN, T::MB)> SB;
+  typedef Mfma<MB> Op;
+  typedef Stage<T::BM, BK> SA;
+  typedef Stage<T::BN, BK> SB;
   // two register stages unless that would hold more than 16 vectors a thread
   static constexpr int ST = (SA::NREG + NB * SB::NREG) <= 16 ? 2 : 1;
   typename Op::Acc acc[NB][TM][TN];
 
-  __device__ __forceinline__ void run(const void* A, int lda, const void* B, int ldb,
+  __device__ __forceinline__ void run(const bf16_t* A, int lda, const bf16_t* B, int ldb,
                                       long long bstride, int M, int N, int K, int m0, int n0,
                                       char* smem) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    void* lds_a = smem;
-    char* lds_b = smem + SA::LDS_ELEMS * (BF ? 2 : 4);
-    const int esz = BF ? 2 : 4;
+    bf16_t* lds_a = (bf16_t*)smem;
+    bf16_t* lds_b = lds_a + SA::LDS_ELEMS;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -264,7 +198,7 @@ struct TileCompute {
         sa[q].template load<AK>(A, lda, m0, M, q * BK, K);
 #pragma unroll
         for (int b = 0; b < NB; ++b)
-          sb[q][b].template load<BKM>((const char*)B + b * bstride * esz, ldb, n0, N, q * BK, K);
+          sb[q][b].template load<BKM>(B + b * bstride, ldb, n0, N, q * BK, K);
       }
     }
     for (int k0 = 0; k0 < K; k0 += ST * BK) {
@@ -276,14 +210,13 @@ struct TileCompute {
           sa[q].template store<AK>(lds_a);
 #pragma unroll
           for (int b = 0; b < NB; ++b)
-            sb[q][b].template store<BKM>(lds_b + b * SB::LDS_ELEMS * esz);
+            sb[q][b].template store<BKM>(lds_b + b * SB::LDS_ELEMS);
           __syncthreads();
           if (kq + ST * BK < K) {
             sa[q].template load<AK>(A, lda, m0, M, kq + ST * BK, K);
 #pragma unroll
             for (int b = 0; b < NB; ++b)
-              sb[q][b].template load<BKM>((const char*)B + b * bstride * esz, ldb, n0, N,
-                                          kq + ST * BK, K);
+              sb[q][b].template load<BKM>(B + b * bstride, ldb, n0, N, kq + ST * BK, K);
           }
           // keep the loads' consumers (the transposes of the next stores)
           // below the products, so that the loads stay in flight under them
@@ -293,13 +226,13 @@ struct TileCompute {
             typename Op::Frag fa[TM];
 #pragma unroll
             for (int i = 0; i < TM; ++i)
-              fa[i] = frag_read<BF, MB, BK>(lds_a, SA::STRIDE, (wm * TM + i) * MB, kk, lane);
+              fa[i] = frag_read<MB>(lds_a, SA::STRIDE, (wm * TM + i) * MB, kk, lane);
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
 #pragma unroll
               for (int j = 0; j < TN; ++j) {
-                typename Op::Frag fb = frag_read<BF, MB, BK>(lds_b + b * SB::LDS_ELEMS * esz,
-                                                             SB::STRIDE, (wn * TN + j) * MB, kk, lane);
+                typename Op::Frag fb = frag_read<MB>(lds_b + b * SB::LDS_ELEMS, SB::STRIDE,
+                                                     (wn * TN + j) * MB, kk, lane);
 #pragma unroll
                 for (int i = 0; i < TM; ++i) acc[b][i][j] = Op::mma(fa[i], fb, acc[b][i][j]);
               }
@@ -311,13 +244,13 @@ struct TileCompute {
   }
 
   static constexpr int smem_bytes() {
-    return (SA::LDS_ELEMS + NB * SB::LDS_ELEMS) * (BF ? 2 : 4);
+    return (SA::LDS_ELEMS + NB * SB::LDS_ELEMS) * 2;
   }
 };
 
-template <bool BF, class T, bool AK, bool BKM, int EPI, int NB>
+template <class T, bool AK, bool BKM, int EPI, int NB>
 __global__ void __launch_bounds__(kThreads) gemm_kernel(GemmArgs g) {
-  typedef TileCompute<BF, T, AK, BKM, NB> TC;
+  typedef TileCompute<T, AK, BKM, NB> TC;
   extern __shared__ __align__(16) char smem[];
   const int M = g.m_rows ? g.st->rows : g.M;
   const int K = g.k_rows ? g.st->rows : g.K;
@@ -326,7 +259,8 @@ __global__ void __launch_bounds__(kThreads) gemm_kernel(GemmArgs g) {
   const int m0 = (tile / gridDim.x) * T::BM, n0 = (tile % gridDim.x) * T::BN;
   if (m0 >= M) return;
   TC tc;
-  tc.run(g.A, g.lda, g.B, g.ldb, g.b_branch_stride, M, N, K, m0, n0, smem);
+  tc.run((const bf16_t*)g.A, g.lda, (const bf16_t*)g.B, g.ldb, g.b_branch_stride, M, N, K, m0, n0,
+         smem);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -339,40 +273,12 @@ __global__ void __launch_bounds__(kThreads) gemm_kernel(GemmArgs g) {
         const int m = m0 + (wm * T::TM + i) * T::MB + acc_row<T::MB>(r, lane);
         const int n = n0 + (wn * T::TN + j) * T::MB + acc_col<T::MB>(lane);
         if (m >= M || n >= N) continue;
-        if constexpr (EPI == EPI_STORE) {
-          float v = tc.acc[0][i][j][r];
-          if (g.bias) v += g.bias[n];
-          if (g.resid) v += g.resid[(long long)m * g.ld_resid + n];
-          if (g.out32) g.out32[(long long)m * g.ld_out32 + n] = v;
-          if (g.out16) g.out16[(long long)m * g.ld_out16 + n] = f2bf(v);
-        } else if constexpr (EPI == EPI_GATE_FWD) {
-          float prod = 1.0f;
+        float v[NB];
 #pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            const float a = tc.acc[b][i][j][r] + g.bias[b * g.bias_branch_stride + n];
-            g.aux[(long long)m * g.ld_aux + b * g.aux_branch + n] = a;
-            prod = (b == 0) ? a : prod * a;
-          }
-          const float v = gelu_f(prod);
-          if (g.out32) g.out32[(long long)m * g.ld_out32 + n] = v;
-          if (g.out16) g.out16[(long long)m * g.ld_out16 + n] = f2bf(v);
-        } else {  // EPI_GATE_BWD: branch count in bias_branch_stride
-          const int nbr = g.bias_branch_stride;
-          float a[3];
-          float prod = 1.0f;
-          for (int b = 0; b < nbr; ++b) {
-            a[b] = g.aux[(long long)m * g.ld_aux + b * g.aux_branch + n];
-            prod = (b == 0) ? a[b] : prod * a[b];
-          }
-          const float dp = tc.acc[0][i][j][r] * gelu_grad_f(prod);
-          for (int b = 0; b < nbr; ++b) {
-            float o = dp;
-            for (int c = 0; c < nbr; ++c)
-              if (c != b) o *= a[c];
-            if (g.out32) g.out32[(long long)m * g.ld_out32 + b * g.aux_branch + n] = o;
-            if (g.out16) g.out16[(long long)m * g.ld_out16 + b * g.aux_branch + n] = f2bf(o);
-          }
-        }
+        for (int b = 0; b < NB; ++b) v[b] = tc.acc[b][i][j][r];
+        EpiOperands<EPI, NB> p;
+        p.load(g, m, n);
+        epi_element<EPI, NB>(g, m, n, v, p);
       }
 }
 
@@ -383,11 +289,11 @@ struct WgradAdamLds {
   static constexpr int BYTES = T::BM * LDG * 4 + T::BM * LDT * 2;
 };
 
-template <bool BF, class T, bool ADAM>
+template <class T, bool ADAM>
 __global__ void __launch_bounds__(kThreads) wgrad_kernel(const WgradProblem* __restrict__ probs,
                                                          int n_probs, const StepState* st,
                                                          WgradAdam ad) {
-  typedef TileCompute<BF, T, false, false, 1> TC;
+  typedef TileCompute<T, false, false, 1> TC;
   extern __shared__ __align__(16) char smem[];
   if constexpr (ADAM) {
     if ((int)blockIdx.x >= ad.tiles) {  // an element-range Adam item
@@ -408,7 +314,7 @@ __global__ void __launch_bounds__(kThreads) wgrad_kernel(const WgradProblem* __r
   const int m0 = (t / pr.tiles_n) * T::BM, n0 = (t % pr.tiles_n) * T::BN;
   const int K = st->rows;
   TC tc;
-  tc.run(pr.dout, pr.M, pr.in, pr.N, 0, pr.M, pr.N, K, m0, n0, smem);
+  tc.run((const bf16_t*)pr.dout, pr.M, (const bf16_t*)pr.in, pr.N, 0, pr.M, pr.N, K, m0, n0, smem);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   if constexpr (!ADAM) {
@@ -520,9 +426,9 @@ typedef TileCfg<128, 64, 32, 2, 1> T128x64;
 typedef TileCfg<64, 128, 32, 1, 2> T64x128;
 typedef TileCfg<128, 128, 32, 2, 2> T128x128;
 
-template <bool BF, class T, bool AK, bool BKM, int EPI, int NB>
+template <class T, bool AK, bool BKM, int EPI, int NB>
 static hipError_t launch_one(const GemmArgs& g, int grid_m_max, hipStream_t s) {
-  typedef TileCompute<BF, T, AK, BKM, NB> TC;
+  typedef TileCompute<T, AK, BKM, NB> TC;
   dim3 grid((g.N + T::BN - 1) / T::BN, (grid_m_max + T::BM - 1) / T::BM);
   if (grid.x == 0 || grid.y == 0) return hipSuccess;
   constexpr int smem = TC::smem_bytes();
@@ -530,44 +436,43 @@ static hipError_t launch_one(const GemmArgs& g, int grid_m_max, hipStream_t s) {
   if constexpr (smem > 64 * 1024) {
     static bool done = false;
     if (!done) {
-      hipError_t e = hipFuncSetAttribute((const void*)gemm_kernel<BF, T, AK, BKM, EPI, NB>,
+      hipError_t e = hipFuncSetAttribute((const void*)gemm_kernel<T, AK, BKM, EPI, NB>,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, smem);
       if (e != hipSuccess) return e;
       done = true;
     }
   }
-  hipLaunchKernelGGL((gemm_kernel<BF, T, AK, BKM, EPI, NB>), grid, dim3(kThreads), smem, s, g);
+  hipLaunchKernelGGL((gemm_kernel<T, AK, BKM, EPI, NB>), grid, dim3(kThreads), smem, s, g);
   return hipGetLastError();
 }
 
-template <bool BF, class T>
+template <class T>
 static hipError_t launch_t(bool ak, bool bk, EpiKind epi, int nb, const GemmArgs& g, int gm,
                            hipStream_t s) {
   if (ak && bk) {  // forward dense layers
-    if (epi == EPI_STORE) return launch_one<BF, T, true, true, EPI_STORE, 1>(g, gm, s);
+    if (epi == EPI_STORE) return launch_one<T, true, true, EPI_STORE, 1>(g, gm, s);
     if (epi == EPI_GATE_FWD) {
-      if (nb == 1) return launch_one<BF, T, true, true, EPI_GATE_FWD, 1>(g, gm, s);
-      if (nb == 2) return launch_one<BF, T, true, true, EPI_GATE_FWD, 2>(g, gm, s);
-      if (nb == 3) return launch_one<BF, T, true, true, EPI_GATE_FWD, 3>(g, gm, s);
+      if (nb == 1) return launch_one<T, true, true, EPI_GATE_FWD, 1>(g, gm, s);
+      if (nb == 2) return launch_one<T, true, true, EPI_GATE_FWD, 2>(g, gm, s);
+      if (nb == 3) return launch_one<T, true, true, EPI_GATE_FWD, 3>(g, gm, s);
     }
   } else if (ak && !bk) {  // adjoint of the input
-    if (epi == EPI_STORE) return launch_one<BF, T, true, false, EPI_STORE, 1>(g, gm, s);
-    if (epi == EPI_GATE_BWD) return launch_one<BF, T, true, false, EPI_GATE_BWD, 1>(g, gm, s);
+    if (epi == EPI_STORE) return launch_one<T, true, false, EPI_STORE, 1>(g, gm, s);
+    if (epi == EPI_GATE_BWD) return launch_one<T, true, false, EPI_GATE_BWD, 1>(g, gm, s);
   }
   return hipErrorInvalidValue;
 }
 
-template <bool BF>
 static hipError_t launch_p(int tile, bool ak, bool bk, EpiKind epi, int nb, const GemmArgs& g,
                            int gm, hipStream_t s) {
   switch (tile) {
-    case TILE_32x32: return launch_t<BF, T32x32>(ak, bk, epi, nb, g, gm, s);
-    case TILE_64x32: return launch_t<BF, T64x32>(ak, bk, epi, nb, g, gm, s);
-    case TILE_32x64: return launch_t<BF, T32x64>(ak, bk, epi, nb, g, gm, s);
-    case TILE_64x64: return launch_t<BF, T64x64>(ak, bk, epi, nb, g, gm, s);
-    case TILE_128x64: return launch_t<BF, T128x64>(ak, bk, epi, nb, g, gm, s);
-    case TILE_64x128: return launch_t<BF, T64x128>(ak, bk, epi, nb, g, gm, s);
-    case TILE_128x128: return launch_t<BF, T128x128>(ak, bk, epi, nb, g, gm, s);
+    case TILE_32x32: return launch_t<T32x32>(ak, bk, epi, nb, g, gm, s);
+    case TILE_64x32: return launch_t<T64x32>(ak, bk, epi, nb, g, gm, s);
+    case TILE_32x64: return launch_t<T32x64>(ak, bk, epi, nb, g, gm, s);
+    case TILE_64x64: return launch_t<T64x64>(ak, bk, epi, nb, g, gm, s);
+    case TILE_128x64: return launch_t<T128x64>(ak, bk, epi, nb, g, gm, s);
+    case TILE_64x128: return launch_t<T64x128>(ak, bk, epi, nb, g, gm, s);
+    case TILE_128x128: return launch_t<T128x128>(ak, bk, epi, nb, g, gm, s);
   }
   return hipErrorInvalidValue;
 }
@@ -578,27 +483,27 @@ hipError_t launch_gemm(int tile, bool bf16, bool a_kmajor, bool b_kmajor, EpiKin
     if (!wide_tile_supported(tile, bf16, epi, nb)) return hipErrorInvalidValue;
     return launch_gemm_wide(tile, a_kmajor, b_kmajor, epi, nb, g, grid_m_max, s);
   }
-  return bf16 ? launch_p<true>(tile, a_kmajor, b_kmajor, epi, nb, g, grid_m_max, s)
-              : launch_p<false>(tile, a_kmajor, b_kmajor, epi, nb, g, grid_m_max, s);
+  return bf16 ? launch_p(tile, a_kmajor, b_kmajor, epi, nb, g, grid_m_max, s)
+              : launch_gemm_fp32(tile, a_kmajor, b_kmajor, epi, nb, g, grid_m_max, s);
 }
 
-template <bool BF, class T>
+template <class T>
 static hipError_t launch_w(const WgradProblem* d_probs, int n_probs, int total_tiles,
                            const StepState* st, hipStream_t s) {
-  typedef TileCompute<BF, T, false, false, 1> TC;
+  typedef TileCompute<T, false, false, 1> TC;
   if (total_tiles == 0) return hipSuccess;
   constexpr int smem = TC::smem_bytes();
   static_assert(smem <= 160 * 1024, "tile does not fit in LDS");
   if constexpr (smem > 64 * 1024) {
     static bool done = false;
     if (!done) {
-      hipError_t e = hipFuncSetAttribute((const void*)wgrad_kernel<BF, T, false>,
+      hipError_t e = hipFuncSetAttribute((const void*)wgrad_kernel<T, false>,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, smem);
       if (e != hipSuccess) return e;
       done = true;
     }
   }
-  hipLaunchKernelGGL((wgrad_kernel<BF, T, false>), dim3(total_tiles), dim3(kThreads), smem, s,
+  hipLaunchKernelGGL((wgrad_kernel<T, false>), dim3(total_tiles), dim3(kThreads), smem, s,
                      d_probs, n_probs, st, WgradAdam{});
   return hipGetLastError();
 }
@@ -606,7 +511,7 @@ static hipError_t launch_w(const WgradProblem* d_probs, int n_probs, int total_t
 template <class T>
 static hipError_t launch_wa(const WgradProblem* d_probs, int n_probs, int wgs,
                             const StepState* st, const WgradAdam& ad, hipStream_t s) {
-  typedef TileCompute<true, T, false, false, 1> TC;
+  typedef TileCompute<T, false, false, 1> TC;
   if (wgs == 0) return hipSuccess;
   constexpr int smem = TC::smem_bytes() > WgradAdamLds<T>::BYTES ? TC::smem_bytes()
                                                                   : WgradAdamLds<T>::BYTES;
@@ -615,13 +520,13 @@ static hipError_t launch_wa(const WgradProblem* d_probs, int n_probs, int wgs,
   if constexpr (smem > 64 * 1024) {
     static bool done = false;
     if (!done) {
-      hipError_t e = hipFuncSetAttribute((const void*)wgrad_kernel<true, T, true>,
+      hipError_t e = hipFuncSetAttribute((const void*)wgrad_kernel<T, true>,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, smem);
       if (e != hipSuccess) return e;
       done = true;
     }
   }
-  hipLaunchKernelGGL((wgrad_kernel<true, T, true>), dim3(wgs), dim3(kThreads), smem, s, d_probs,
+  hipLaunchKernelGGL((wgrad_kernel<T, true>), dim3(wgs), dim3(kThreads), smem, s, d_probs,
                      n_probs, st, ad);
   return hipGetLastError();
 }
@@ -643,17 +548,16 @@ hipError_t launch_wgrad_adam(int tile, const WgradProblem* p, int n, int tt, int
   return hipErrorInvalidValue;
 }
 
-template <bool BF>
 static hipError_t launch_wp(int tile, const WgradProblem* p, int n, int tt, const StepState* st,
                             hipStream_t s) {
   switch (tile) {
-    case TILE_32x32: return launch_w<BF, T32x32>(p, n, tt, st, s);
-    case TILE_64x32: return launch_w<BF, T64x32>(p, n, tt, st, s);
-    case TILE_32x64: return launch_w<BF, T32x64>(p, n, tt, st, s);
-    case TILE_64x64: return launch_w<BF, T64x64>(p, n, tt, st, s);
-    case TILE_128x64: return launch_w<BF, T128x64>(p, n, tt, st, s);
-    case TILE_64x128: return launch_w<BF, T64x128>(p, n, tt, st, s);
-    case TILE_128x128: return launch_w<BF, T128x128>(p, n, tt, st, s);
+    case TILE_32x32: return launch_w<T32x32>(p, n, tt, st, s);
+    case TILE_64x32: return launch_w<T64x32>(p, n, tt, st, s);
+    case TILE_32x64: return launch_w<T32x64>(p, n, tt, st, s);
+    case TILE_64x64: return launch_w<T64x64>(p, n, tt, st, s);
+    case TILE_128x64: return launch_w<T128x64>(p, n, tt, st, s);
+    case TILE_64x128: return launch_w<T64x128>(p, n, tt, st, s);
+    case TILE_128x128: return launch_w<T128x128>(p, n, tt, st, s);
   }
   return hipErrorInvalidValue;
 }
@@ -664,8 +568,8 @@ hipError_t launch_wgrad(int tile, bool bf16, const WgradProblem* d_probs, int n_
     if (!bf16) return hipErrorInvalidValue;
     return launch_wgrad_wide(tile, d_probs, n_probs, total_tiles, st, part, s);
   }
-  return bf16 ? launch_wp<true>(tile, d_probs, n_probs, total_tiles, st, s)
-              : launch_wp<false>(tile, d_probs, n_probs, total_tiles, st, s);
+  return bf16 ? launch_wp(tile, d_probs, n_probs, total_tiles, st, s)
+              : launch_wgrad_fp32(tile, d_probs, n_probs, total_tiles, st, s);
 }
 
 }  // namespace edpc
