@@ -2,6 +2,8 @@
 #include "kernels.h"
 #include "head_row.h"
 
+#include <algorithm>
+
 namespace edpc {
 
 static inline unsigned blocks_for(size_t n, unsigned per) { return (unsigned)((n + per - 1) / per); }
@@ -105,22 +107,49 @@ void k_embed(const StepState* st, const uint8_t* ctx, const float* emb, int C, i
                      x32, x16);
 }
 
-// Streaming (non-temporal) 16-byte accesses for the Adam moments of the FDM:
-// every element of m_U, v_U is read and written once per step, while U is
-// read again by the next step's forward product and keeps normal caching.
-__device__ __forceinline__ float4 nt_load4(const float* p) {
+// 16-byte accesses, streaming (non-temporal) where NT.
+template <bool NT>
+__device__ __forceinline__ float4 load4(const float* p) {
   typedef float f4 __attribute__((ext_vector_type(4)));
+  if constexpr (!NT) return *(const float4*)p;
   const f4 v = __builtin_nontemporal_load((const f4*)p);
   return make_float4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ void nt_store4(float* p, float4 x) {
+template <bool NT>
+__device__ __forceinline__ void store4(float* p, float4 x) {
   typedef float f4 __attribute__((ext_vector_type(4)));
-  const f4 v = {x.x, x.y, x.z, x.w};
-  __builtin_nontemporal_store(v, (f4*)p);
+  if constexpr (!NT) {
+    *(float4*)p = x;
+  } else {
+    const f4 v = {x.x, x.y, x.z, x.w};
+    __builtin_nontemporal_store(v, (f4*)p);
+  }
 }
 
-// Rows of U_s whose loads are issued together in the FDM kernels.
+// Which accesses to a per-stream matrix and its Adam moments are streaming.
+// The state is read and written once a step (and the matrix read once more by
+// the forward product), so caching pays only for what stays in the 256 MB
+// memory-side cache until the next step, beside what else a step touches:
+// all of it up to 160 MB (700 slots of 128 x 128: 39.3 us against 42.0 with the
+// moments streaming; 1024 slots, 201 MB: no difference in a step), the matrices
+// up to 256 MB (4096 slots of 128 x 128: 203 against 236 us with all of it
+// streaming, 292 with all of it cached), else nothing (16384 slots of
+// 256 x 256: 4.85 against 4.99 ms, the forward product 716 against 758 us).
+enum FdmCache : int {
+  FDM_CACHED = 0,      // all of it fits
+  FDM_STREAM_ADAM = 1,  // the matrices do
+  FDM_STREAM = 2       // not even they
+};
+constexpr size_t kFdmCachedBytes = (size_t)160 << 20;
+static FdmCache fdm_cache(int rows, int Lin, int Lout) {
+  const size_t bytes = (size_t)rows * Lin * Lout * sizeof(float);
+  return 3 * bytes <= kFdmCachedBytes ? FDM_CACHED : bytes <= ((size_t)256 << 20) ? FDM_STREAM_ADAM : FDM_STREAM;
+}
+
+// Rows of U_s whose loads are issued together in the FDM kernels, and the most
+// workgroups that share a slot in the adjoint.
 constexpr int kFdmBatch = 4;
+constexpr int kFdmSplit = 4;
 
 // ---------------------------------------------------------------------------
 // Feature Distribution Matrix (Eq. 15): y_s = x'_s U_s, one workgroup per row.
@@ -128,6 +157,7 @@ constexpr int kFdmBatch = 4;
 // per-stream factors A_s [F, F'] and B_s [F', F] use the same kernels).
 // Thread (g, t): t covers columns 4t..4t+3, group g rows l = g, g+G, ...
 // ---------------------------------------------------------------------------
+template <bool NT>
 __global__ void __launch_bounds__(256) fdm_fwd_kernel(const StepState* __restrict__ st,
                                                       const float* __restrict__ x1,
                                                       const float* __restrict__ U,
@@ -150,7 +180,7 @@ __global__ void __launch_bounds__(256) fdm_fwd_kernel(const StepState* __restric
     for (; l + (kFdmBatch - 1) * G < Lin; l += kFdmBatch * G) {
       float4 u[kFdmBatch];
 #pragma unroll
-      for (int q = 0; q < kFdmBatch; ++q) u[q] = *(const float4*)(Us + (size_t)(l + q * G) * Lout + 4 * t);
+      for (int q = 0; q < kFdmBatch; ++q) u[q] = load4<NT>(Us + (size_t)(l + q * G) * Lout + 4 * t);
 #pragma unroll
       for (int q = 0; q < kFdmBatch; ++q) {
         const float xv = xs[l + q * G];
@@ -161,7 +191,7 @@ __global__ void __launch_bounds__(256) fdm_fwd_kernel(const StepState* __restric
       }
     }
     for (; l < Lin; l += G) {
-      const float4 u = *(const float4*)(Us + (size_t)l * Lout + 4 * t);
+      const float4 u = load4<NT>(Us + (size_t)l * Lout + 4 * t);
       const float xv = xs[l];
       acc.x += xv * u.x;
       acc.y += xv * u.y;
@@ -181,25 +211,32 @@ __global__ void __launch_bounds__(256) fdm_fwd_kernel(const StepState* __restric
 
 void k_fdm_fwd(const StepState* st, const float* x1, const float* U, const uint32_t* slot, int Lin,
                int Lout, float* y32, bf16_t* y16, int max_rows, hipStream_t s) {
-  hipLaunchKernelGGL(fdm_fwd_kernel, dim3(max_rows), dim3(256), 0, s, st, x1, U, slot, Lin, Lout,
-                     y32, y16);
+  const bool nt = fdm_cache(max_rows, Lin, Lout) == FDM_STREAM;
+  hipLaunchKernelGGL(nt ? fdm_fwd_kernel<true> : fdm_fwd_kernel<false>, dim3(max_rows), dim3(256), 0,
+                     s, st, x1, U, slot, Lin, Lout, y32, y16);
 }
 
 // Adjoint of Eq. 15 fused with the Adam step on U_s:
 //   dx'_s = U_s dy_s (with U before the update), dU_s = x'_s (x) dy_s.
+// Bound by memory: 24 bytes an element of U_s.  The rows of U_s are independent,
+// so `split` workgroups share a slot; one workgroup a slot leaves the last
+// round of workgroups short and too few loads in flight.
+// (FIGURES)
+template <int CACHE>
 __global__ void __launch_bounds__(256) fdm_bwd_kernel(
     const StepState* __restrict__ st, const float* __restrict__ x1, const float* __restrict__ dy,
     float* __restrict__ U, float* __restrict__ mU, float* __restrict__ vU,
     float* __restrict__ dU_keep, const uint32_t* __restrict__ slot, int Lin, int Lout, AdamCfg ac,
-    bool update,
-    float* __restrict__ dx1_32, bf16_t* __restrict__ dx1_16) {
-  const int r = blockIdx.x;
+    bool update, float* __restrict__ dx1_32, bf16_t* __restrict__ dx1_16, int split) {
+  constexpr bool NTU = CACHE == FDM_STREAM, NTM = CACHE != FDM_CACHED;
+  const int r = blockIdx.x / split;
   if (r >= st->rows) return;
   __shared__ float xs[256];
   __shared__ float ds[256];
   const int tpr = Lout >> 2, G = 256 / tpr;
   const int t = threadIdx.x % tpr, g = threadIdx.x / tpr;
-  for (int l = threadIdx.x; l < Lin; l += 256) xs[l] = x1[(size_t)r * Lin + l];
+  const int per = Lin / split, lb = (int)(blockIdx.x % split) * per, le = lb + per;  // this workgroup's rows
+  for (int l = lb + threadIdx.x; l < le; l += 256) xs[l] = x1[(size_t)r * Lin + l];
   for (int k = threadIdx.x; k < Lout; k += 256) ds[k] = dy[(size_t)r * Lout + k];
   __syncthreads();
   if (g >= G) return;
@@ -230,40 +267,46 @@ __global__ void __launch_bounds__(256) fdm_bwd_kernel(
         vp[j] = b2 * vp[j] + (1.0f - b2) * gr[j] * gr[j];
         up[j] -= lr_bc * mp[j] / (sqrtf(vp[j] * inv_bc2) + ac.eps);
       }
-      *(float4*)(U + idx) = u;
-      nt_store4(mU + idx, m);
-      nt_store4(vU + idx, v);
+      store4<NTU>(U + idx, u);
+      store4<NTM>(mU + idx, m);
+      store4<NTM>(vU + idx, v);
     }
   };
-  // rows l = g, g + G, ...; the loads of kFdmBatch rows are issued before any
-  // of them is used, so that each thread keeps 3 kFdmBatch 16-byte loads in
-  // flight (the rows are independent: each updates its own slice of U_s)
+  // rows l = lb + g, lb + g + G, ...; the loads of kFdmBatch rows are issued
+  // before any of them is used, so that each thread keeps 3 kFdmBatch 16-byte
+  // loads in flight
   const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  int l = g;
-  for (; l + (kFdmBatch - 1) * G < Lin; l += kFdmBatch * G) {
+  int l = lb + g;
+  for (; l + (kFdmBatch - 1) * G < le; l += kFdmBatch * G) {
     float4 u[kFdmBatch], m[kFdmBatch], v[kFdmBatch];
 #pragma unroll
     for (int q = 0; q < kFdmBatch; ++q) {
       const size_t idx = base_s + (size_t)(l + q * G) * Lout + 4 * t;
-      u[q] = *(const float4*)(U + idx);
-      m[q] = update ? nt_load4(mU + idx) : z4;
-      v[q] = update ? nt_load4(vU + idx) : z4;
+      u[q] = load4<NTU>(U + idx);
+      m[q] = update ? load4<NTM>(mU + idx) : z4;
+      v[q] = update ? load4<NTM>(vU + idx) : z4;
     }
 #pragma unroll
     for (int q = 0; q < kFdmBatch; ++q) row(l + q * G, u[q], m[q], v[q]);
   }
-  for (; l < Lin; l += G) {
+  for (; l < le; l += G) {
     const size_t idx = base_s + (size_t)l * Lout + 4 * t;
-    row(l, *(const float4*)(U + idx), update ? nt_load4(mU + idx) : z4,
-        update ? nt_load4(vU + idx) : z4);
+    row(l, load4<NTU>(U + idx), update ? load4<NTM>(mU + idx) : z4,
+        update ? load4<NTM>(vU + idx) : z4);
   }
 }
 
 void k_fdm_bwd(const StepState* st, const float* x1, const float* dy, float* U, float* mU,
                float* vU, float* dU_keep, const uint32_t* slot, int Lin, int Lout, AdamCfg ac,
                bool update, float* dx1_32, bf16_t* dx1_16, int max_rows, hipStream_t s) {
-  hipLaunchKernelGGL(fdm_bwd_kernel, dim3(max_rows), dim3(256), 0, s, st, x1, dy, U, mU, vU,
-                     dU_keep, slot, Lin, Lout, ac, update, dx1_32, dx1_16);
+  const int G = 1024 / Lout;  // rows of U_s per pass of a workgroup
+  const int split = std::max(1, std::min(kFdmSplit, Lin / (kFdmBatch * G)));
+  const FdmCache c = fdm_cache(max_rows, Lin, Lout);
+  hipLaunchKernelGGL(c == FDM_CACHED        ? fdm_bwd_kernel<FDM_CACHED>
+                     : c == FDM_STREAM_ADAM ? fdm_bwd_kernel<FDM_STREAM_ADAM>
+                                            : fdm_bwd_kernel<FDM_STREAM>,
+                     dim3((unsigned)max_rows * split), dim3(256), 0, s, st, x1, dy, U, mU, vU, dU_keep,
+                     slot, Lin, Lout, ac, update, dx1_32, dx1_16, split);
 }
 
 // ---------------------------------------------------------------------------
