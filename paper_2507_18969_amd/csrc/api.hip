@@ -356,12 +356,7 @@ edpc_status edpc_model_step(edpc_model* mh, const uint8_t* d_ctx, const uint8_t*
     out.update = (flags & EDPC_STEP_UPDATE) != 0;
     out.backward = bwd;
     out.keep_fdm_grad = (flags & EDPC_STEP_KEEP_FDM_GRAD) != 0 && !out.update;
-    if (out.keep_fdm_grad && !m.dUkeep) {
-      void* p = nullptr;
-      hip_check(hipMalloc(&p, m.n_slots * (size_t)m.L * m.L * sizeof(float)), "hipMalloc");
-      m.allocs.push_back(p);
-      m.dUkeep = (float*)p;
-    }
+    if (out.keep_fdm_grad && !m.dUkeep) m.dUkeep = m.mem.take<float>(m.n_slots * (size_t)m.L * m.L);
     if (out.keep_fdm_grad)  // slots outside this call get a zero gradient
       hip_check(hipMemsetAsync(m.dUkeep, 0, m.n_slots * (size_t)m.L * m.L * sizeof(float), s), "memset");
     const uint32_t tau = out.update ? (uint32_t)(m.tau + 1) : (uint32_t)(m.tau > 0 ? m.tau : 1);
@@ -754,14 +749,12 @@ edpc_status edpc_rc_encode(const uint32_t* d_cum, const uint8_t* d_sym, size_t n
     if (n_streams == 0) fail(EDPC_E_INVALID_ARG, "n_streams must be >= 1");
     if (cap < 2 * n_steps + 2) fail(EDPC_E_INVALID_ARG, "cap_per_stream < 2 * n_steps + 2");
     hipStream_t s = S(stream);
-    uint64_t* d_len = nullptr;
-    hip_check(hipMalloc(&d_len, n_streams * 8), "hipMalloc");
-    k_rc_table_encode(d_cum, d_sym, n_steps, n_streams, d_out, cap, d_len, s);
     std::vector<uint64_t> l(n_streams);
-    hipError_t e = hipMemcpyAsync(l.data(), d_len, n_streams * 8, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFree(d_len);
-    hip_check(e, "rc encode");
+    Scratch scratch(n_streams * 8, s);
+    uint64_t* d_len = (uint64_t*)scratch.get();
+    k_rc_table_encode(d_cum, d_sym, n_steps, n_streams, d_out, cap, d_len, s);
+    hip_check(hipMemcpyAsync(l.data(), d_len, n_streams * 8, hipMemcpyDeviceToHost, s), "copy");
+    hip_check(hipStreamSynchronize(s), "rc encode");
     for (size_t i = 0; i < n_streams; ++i) h_out_lens[i] = (uint32_t)l[i];
     return EDPC_OK;
   });
@@ -833,15 +826,11 @@ edpc_status edpc_rc_decode(const uint32_t* d_cum, const uint8_t* d_in, const uin
     if (n_streams == 0) fail(EDPC_E_INVALID_ARG, "n_streams must be >= 1");
     hipStream_t s = S(stream);
     std::vector<uint64_t> l(h_in_lens, h_in_lens + n_streams);
-    uint64_t* d_len = nullptr;
-    hip_check(hipMalloc(&d_len, n_streams * 8), "hipMalloc");
-    hipError_t e = hipMemcpyAsync(d_len, l.data(), n_streams * 8, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) {
-      k_rc_table_decode(d_cum, d_in, d_len, cap, n_steps, n_streams, d_sym, s);
-      e = hipStreamSynchronize(s);
-    }
-    (void)hipFree(d_len);
-    hip_check(e, "rc decode");
+    Scratch scratch(n_streams * 8, s);
+    uint64_t* d_len = (uint64_t*)scratch.get();
+    hip_check(hipMemcpyAsync(d_len, l.data(), n_streams * 8, hipMemcpyHostToDevice, s), "copy");
+    k_rc_table_decode(d_cum, d_in, d_len, cap, n_steps, n_streams, d_sym, s);
+    hip_check(hipStreamSynchronize(s), "rc decode");
     return EDPC_OK;
   });
 }

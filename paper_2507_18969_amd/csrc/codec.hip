@@ -141,17 +141,6 @@ Session::~Session() {
   if (s) (void)hipStreamSynchronize(s);
   for (auto& g : graphs) (void)hipGraphExecDestroy(g.second);
   if (cap) (void)hipStreamDestroy(cap);
-  model.reset();
-  for (void* p : allocs) (void)hipFree(p);
-}
-
-template <class T>
-T* Session::dalloc(size_t cnt) {
-  void* p = nullptr;
-  if (cnt == 0) cnt = 1;
-  hip_check(hipMalloc(&p, cnt * sizeof(T)), "hipMalloc");
-  allocs.push_back(p);
-  return (T*)p;
 }
 
 int Session::rows_at(uint64_t i) const {
@@ -165,6 +154,11 @@ int Session::bucket(int rows) const {
   // grid rows of a captured window: rows rounded up to a multiple of 128
   const int b = ((rows + 127) / 128) * 128;
   return std::min(b, (int)model->max_rows);
+}
+
+uint64_t Session::bucket_end(int rows) const {
+  const int below = (rows - 1) / 128 * 128;  // rows of the next smaller bucket
+  return below > 0 ? (uint64_t)lens_sorted[below] : maxlen;
 }
 
 void Session::step_direct(uint64_t i, int grid_rows, bool explicit_step, hipStream_t st, int rel) {
@@ -200,7 +194,7 @@ void Session::run(uint64_t k) {
       const int b = bucket(rows);
       if (bucket(rows_at(i + graph_steps - 1)) == b) {
         auto it = graphs.find(b);
-        if (it == graphs.end()) {
+        if (it == graphs.end() && bucket_end(rows) - i >= kGraphMinSteps) {
           if (!cap) hip_check(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking), "stream");
           TraceRange range("graph capture");
           hipGraph_t g = nullptr;
@@ -219,12 +213,14 @@ void Session::run(uint64_t k) {
           hip_check(e, "graph instantiate");
           it = graphs.emplace(b, ex).first;
         }
-        // the captured steps advance from the device step counter
-        TraceRange range("graph window");
-        k_step_set(model->st, (int)i - 1, s);
-        hip_check(hipGraphLaunch(it->second, s), "graph launch");
-        i += graph_steps;
-        continue;
+        if (it != graphs.end()) {
+          // the captured steps advance from the device step counter
+          TraceRange range("graph window");
+          k_step_set(model->st, (int)i - 1, s);
+          hip_check(hipGraphLaunch(it->second, s), "graph launch");
+          i += graph_steps;
+          continue;
+        }
       }
     }
     {
@@ -256,19 +252,14 @@ void common_setup(Session& ss, const KernelConfig* kc) {
   }
   hip_check(hipMemcpyAsync(ss.model->slot, perm.data(), std::min(n, rows) * sizeof(uint32_t),
                            hipMemcpyHostToDevice, ss.s), "copy");
-  ss.d_lens_sorted = ss.dalloc<int64_t>(n);
-  hip_check(hipMemcpyAsync(ss.d_lens_sorted, ss.lens_sorted.data(), n * sizeof(int64_t),
-                           hipMemcpyHostToDevice, ss.s), "copy");
-  ss.d_lens = ss.dalloc<uint64_t>(n);
-  hip_check(hipMemcpyAsync(ss.d_lens, ss.lens.data(), n * sizeof(uint64_t), hipMemcpyHostToDevice,
-                           ss.s), "copy");
   std::vector<uint64_t> off(n);
   uint64_t o = 0;
   for (size_t s = 0; s < n; ++s) { off[s] = o; o += ss.lens[s]; }
-  ss.d_off = ss.dalloc<uint64_t>(n);
-  hip_check(hipMemcpyAsync(ss.d_off, off.data(), n * sizeof(uint64_t), hipMemcpyHostToDevice, ss.s),
-            "copy");
-  ss.d_crc = ss.dalloc<uint32_t>(n);
+  ss.tables.add(&ss.d_lens_sorted, ss.lens_sorted);
+  ss.tables.add(&ss.d_lens, ss.lens);
+  ss.tables.add(&ss.d_off, off);
+  ss.tables.commit(ss.mem, ss.s);
+  ss.d_crc = ss.mem.take<uint32_t>(n);
   ss.sched.lens_sorted = ss.d_lens_sorted;
   ss.sched.n = (int)n;
   ss.sched.context = (int)ss.cfg.context;
@@ -299,12 +290,11 @@ std::unique_ptr<Session> encoder_begin(const edpc_config& cfg, const uint8_t* d_
   std::vector<uint64_t> pay_off(n), pay_cap(n);
   uint64_t o = 0;
   for (size_t i = 0; i < n; ++i) { pay_off[i] = o; pay_cap[i] = 2 * lens[i] + 8; o += pay_cap[i]; }
-  ss->d_pay = ss->dalloc<uint8_t>(o);
-  ss->d_pay_off = ss->dalloc<uint64_t>(n);
-  ss->d_pay_cap = ss->dalloc<uint64_t>(n);
-  hip_check(hipMemcpyAsync(ss->d_pay_off, pay_off.data(), n * 8, hipMemcpyHostToDevice, s), "copy");
-  hip_check(hipMemcpyAsync(ss->d_pay_cap, pay_cap.data(), n * 8, hipMemcpyHostToDevice, s), "copy");
-  ss->d_enc = ss->dalloc<RcEnc>(n);
+  ss->d_pay = ss->mem.take<uint8_t>(o);
+  ss->tables.add(&ss->d_pay_off, pay_off);
+  ss->tables.add(&ss->d_pay_cap, pay_cap);
+  ss->tables.commit(ss->mem, s);
+  ss->d_enc = ss->mem.take<RcEnc>(n);
   ss->io.src = d_in;
   ss->io.pay = ss->d_pay;
   ss->io.pay_off = ss->d_pay_off;
@@ -345,10 +335,10 @@ size_t encoder_finish(Session& ss, uint8_t* d_out, size_t out_cap) {
     ss.out_cap = total;
     throw e;
   }
-  uint64_t* d_dst_off = ss.dalloc<uint64_t>(ss.n);
-  uint64_t* d_pl = ss.dalloc<uint64_t>(ss.n);
-  hip_check(hipMemcpyAsync(d_dst_off, dst_off.data(), ss.n * 8, hipMemcpyHostToDevice, ss.s), "copy");
-  hip_check(hipMemcpyAsync(d_pl, h.pay_lens.data(), ss.n * 8, hipMemcpyHostToDevice, ss.s), "copy");
+  uint64_t *d_dst_off = nullptr, *d_pl = nullptr;
+  ss.tables.add(&d_dst_off, dst_off);
+  ss.tables.add(&d_pl, h.pay_lens);
+  ss.tables.commit(ss.mem, ss.s);
   hip_check(hipMemcpyAsync(d_out, hb.data(), hb.size(), hipMemcpyHostToDevice, ss.s), "copy");
   k_gather_payloads(ss.d_pay, ss.d_pay_off, d_pl, d_dst_off, d_out, (int)ss.n, ss.s);
   hip_check(hipStreamSynchronize(ss.s), "encode finish");
@@ -399,11 +389,10 @@ std::unique_ptr<Session> decoder_begin(const uint8_t* d_in, size_t in_len, uint8
   std::vector<uint64_t> pay_off(n);
   uint64_t o = h.header_len;
   for (size_t i = 0; i < n; ++i) { pay_off[i] = o; o += h.pay_lens[i]; }
-  ss->d_pay_off = ss->dalloc<uint64_t>(n);
-  ss->d_pay_cap = ss->dalloc<uint64_t>(n);
-  hip_check(hipMemcpyAsync(ss->d_pay_off, pay_off.data(), n * 8, hipMemcpyHostToDevice, s), "copy");
-  hip_check(hipMemcpyAsync(ss->d_pay_cap, h.pay_lens.data(), n * 8, hipMemcpyHostToDevice, s), "copy");
-  ss->d_dec = ss->dalloc<RcDec>(n);
+  ss->tables.add(&ss->d_pay_off, pay_off);
+  ss->tables.add(&ss->d_pay_cap, h.pay_lens);
+  ss->tables.commit(ss->mem, s);
+  ss->d_dec = ss->mem.take<RcDec>(n);
   ss->io.dst = d_out;
   ss->io.pay_in = d_in;
   ss->io.pay_off = ss->d_pay_off;

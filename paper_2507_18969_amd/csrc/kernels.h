@@ -148,11 +148,20 @@ void k_emb_grad(const StepState* st, const uint8_t* ctx, const float* dx, int C,
 void k_adam(const StepState* st, float* p, const float* g, float* m, float* v, bf16_t* p16,
             size_t n, AdamCfg ac, hipStream_t s);
 
-// Counter-based initialisation: dst[j] = fl32(a_j * bound), a_j from
-// SplitMix64(seed + (tid << 40) + start + j).
-void k_init_uniform(float* dst, size_t n, uint64_t seed, uint32_t tid, uint64_t start, float bound,
+// Counter-based initialisation: element j of a tensor is fl32(a_j * bound), a_j
+// from SplitMix64(seed + (tid << 40) + j); tid 0: every element is `bound`.
+// The shared parameters (with their BF16 copies, where p16), zero moments and
+// gradients, padding zero; and a per-stream matrix (n elements, a multiple of 4)
+// with zero moments.
+struct InitTensor {
+  size_t off, numel;
+  uint32_t tid;
+  float bound;
+};
+void k_init_shared(const InitTensor* t, int n, size_t total, uint64_t seed, float* p, float* m,
+                   float* v, float* g, bf16_t* p16, hipStream_t s);
+void k_init_streams(float* u, float* m, float* v, size_t n, uint64_t seed, uint32_t tid, float bound,
                     hipStream_t s);
-void k_fill(float* dst, size_t n, float v, hipStream_t s);
 void k_to_bf16(const float* src, bf16_t* dst, size_t n, hipStream_t s);
 
 // Coder lanes.

@@ -967,30 +967,69 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t x) {
   return z ^ (z >> 31);
 }
 
-__global__ void init_uniform_kernel(float* __restrict__ dst, size_t n, uint64_t seed, uint32_t tid,
-                                    uint64_t start, float bound) {
-  const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const uint64_t r = splitmix64(seed + ((uint64_t)tid << 40) + start + j);
-  const int k = (int)(r >> 40) - (1 << 23);
+__device__ __forceinline__ float init_value(uint64_t counter, float bound) {
+  const int k = (int)(splitmix64(counter) >> 40) - (1 << 23);
   const float a = (float)k * (1.0f / 8388608.0f);
-  dst[j] = a * bound;
+  return a * bound;
 }
 
-void k_init_uniform(float* dst, size_t n, uint64_t seed, uint32_t tid, uint64_t start, float bound,
+// Tensors [0, n) of one launch, by increasing offset; elements begin .. end - 1
+// of the flat buffers, padding between tensors included.
+constexpr int kInitTensors = 64;
+struct InitBatch {
+  InitTensor t[kInitTensors];
+  int n;
+  size_t begin, end;
+};
+
+__global__ void __launch_bounds__(256) init_shared_kernel(InitBatch b, uint64_t seed, float* __restrict__ p,
+                                                          float* __restrict__ m, float* __restrict__ v,
+                                                          float* __restrict__ g, bf16_t* __restrict__ p16) {
+  const size_t e = b.begin + (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= b.end) return;
+  int lo = 0, hi = b.n;  // the last tensor that starts at or before e
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (b.t[mid].off <= e) lo = mid; else hi = mid;
+  }
+  const InitTensor t = b.t[lo];
+  const size_t j = e - t.off;
+  const float x = j >= t.numel ? 0.0f : t.tid ? init_value(seed + ((uint64_t)t.tid << 40) + j, t.bound) : t.bound;
+  p[e] = x;
+  m[e] = v[e] = g[e] = 0.0f;
+  if (p16) p16[e] = f2bf(x);
+}
+
+void k_init_shared(const InitTensor* t, int n, size_t total, uint64_t seed, float* p, float* m,
+                   float* v, float* g, bf16_t* p16, hipStream_t s) {
+  for (int i = 0; i < n; i += kInitTensors) {
+    InitBatch b;
+    b.n = std::min(kInitTensors, n - i);
+    for (int k = 0; k < b.n; ++k) b.t[k] = t[i + k];
+    b.begin = i == 0 ? 0 : t[i].off;
+    b.end = i + b.n < n ? t[i + b.n].off : total;
+    hipLaunchKernelGGL(init_shared_kernel, dim3(blocks_for(b.end - b.begin, 256)), dim3(256), 0, s, b,
+                       seed, p, m, v, g, p16);
+  }
+}
+
+// n a multiple of 4
+__global__ void __launch_bounds__(256) init_streams_kernel(float* __restrict__ u, float* __restrict__ m,
+                                                           float* __restrict__ v, size_t n, uint64_t counter,
+                                                           float bound) {
+  const size_t j = 4 * ((size_t)blockIdx.x * 256 + threadIdx.x);
+  if (j >= n) return;
+  *(float4*)(u + j) = make_float4(init_value(counter + j, bound), init_value(counter + j + 1, bound),
+                                  init_value(counter + j + 2, bound), init_value(counter + j + 3, bound));
+  const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+  *(float4*)(m + j) = z;
+  *(float4*)(v + j) = z;
+}
+
+void k_init_streams(float* u, float* m, float* v, size_t n, uint64_t seed, uint32_t tid, float bound,
                     hipStream_t s) {
-  if (n == 0) return;
-  hipLaunchKernelGGL(init_uniform_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, dst, n, seed,
-                     tid, start, bound);
-}
-
-__global__ void fill_kernel(float* dst, size_t n, float v) {
-  const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n) dst[j] = v;
-}
-void k_fill(float* dst, size_t n, float v, hipStream_t s) {
-  if (n == 0) return;
-  hipLaunchKernelGGL(fill_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, dst, n, v);
+  hipLaunchKernelGGL(init_streams_kernel, dim3(blocks_for(n / 4, 256)), dim3(256), 0, s, u, m, v, n,
+                     seed + ((uint64_t)tid << 40), bound);
 }
 
 __global__ void to_bf16_kernel(const float* src, bf16_t* dst, size_t n) {

@@ -221,44 +221,32 @@ double mutual_info(const float* d_z, size_t dz, const float* d_y, size_t dy, siz
   if (c < 2 || c > 32768) fail(EDPC_E_INVALID_ARG, "number of samples must be in 2..32768");
   if (v < 1 || v >= c || v > (uint32_t)kKsgMaxV) fail(EDPC_E_INVALID_ARG, "v must be in 1..min(16, c - 1)");
   if (dz < 1 || dy < 1 || dz > (1u << 20) || dy > (1u << 20)) fail(EDPC_E_INVALID_ARG, "bad dimension");
-  std::vector<void*> tmp;
-  auto alloc = [&](size_t bytes) {
-    void* p = nullptr;
-    hip_check(hipMalloc(&p, bytes), "hipMalloc");
-    tmp.push_back(p);
-    return p;
-  };
-  double mi = 0.0;
-  try {
-    float* Dz = (float*)alloc(c * c * sizeof(float));
-    float* Dy = (float*)alloc(c * c * sizeof(float));
-    int32_t* cnt = d_counts ? d_counts : (int32_t*)alloc(2 * c * sizeof(int32_t));
-    const unsigned tiles = (unsigned)((c + kKsgTile - 1) / kKsgTile);
-    const dim3 grid(tiles * (tiles + 1) / 2, 2);
-    const bool vec = dz % 4 == 0 && dy % 4 == 0 && ((uintptr_t)d_z | (uintptr_t)d_y) % 16 == 0;
-    hipLaunchKernelGGL(vec ? maxnorm_kernel<true> : maxnorm_kernel<false>, grid, dim3(256), 0, s, d_z,
-                       (int)dz, Dz, d_y, (int)dy, Dy, (int)c);
-    const dim3 sgrid((unsigned)((c + 3) / 4));
-    hipLaunchKernelGGL(v <= 4 ? ksg_select_kernel<4> : ksg_select_kernel<kKsgMaxV>, sgrid, dim3(256),
-                       0, s, Dz, Dy, (int)c, (int)v, d_eps, cnt);
-    hip_check(hipGetLastError(), "ksg launch");
-    std::vector<int32_t> h(2 * c);
-    hip_check(hipMemcpyAsync(h.data(), cnt, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s),
-              "copy");
-    hip_check(hipStreamSynchronize(s), "ksg");
-    // psi(n) = -gamma + H(n - 1) at integers
-    std::vector<double> H(c + 2, 0.0);
-    for (size_t m = 1; m < H.size(); ++m) H[m] = H[m - 1] + 1.0 / (double)m;
-    const double gamma = 0.57721566490153286061;
-    auto psi = [&](size_t n) { return -gamma + H[n - 1]; };
-    double sum = 0.0;
-    for (size_t i = 0; i < c; ++i) sum += psi((size_t)h[2 * i] + 1) + psi((size_t)h[2 * i + 1] + 1);
-    mi = psi(v) + psi(c) - sum / (double)c;
-  } catch (...) {
-    for (void* p : tmp) (void)hipFree(p);
-    throw;
-  }
-  for (void* p : tmp) (void)hipFree(p);
+  std::vector<int32_t> h(2 * c);
+  const size_t dist = (c * c * sizeof(float) + 255) & ~(size_t)255;
+  Scratch scratch(2 * dist + 2 * c * sizeof(int32_t), s);
+  float* Dz = (float*)scratch.get();
+  float* Dy = (float*)((char*)scratch.get() + dist);
+  int32_t* cnt = d_counts ? d_counts : (int32_t*)((char*)scratch.get() + 2 * dist);
+  const unsigned tiles = (unsigned)((c + kKsgTile - 1) / kKsgTile);
+  const dim3 grid(tiles * (tiles + 1) / 2, 2);
+  const bool vec = dz % 4 == 0 && dy % 4 == 0 && ((uintptr_t)d_z | (uintptr_t)d_y) % 16 == 0;
+  hipLaunchKernelGGL(vec ? maxnorm_kernel<true> : maxnorm_kernel<false>, grid, dim3(256), 0, s, d_z,
+                     (int)dz, Dz, d_y, (int)dy, Dy, (int)c);
+  const dim3 sgrid((unsigned)((c + 3) / 4));
+  hipLaunchKernelGGL(v <= 4 ? ksg_select_kernel<4> : ksg_select_kernel<kKsgMaxV>, sgrid, dim3(256),
+                     0, s, Dz, Dy, (int)c, (int)v, d_eps, cnt);
+  hip_check(hipGetLastError(), "ksg launch");
+  hip_check(hipMemcpyAsync(h.data(), cnt, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s),
+            "copy");
+  hip_check(hipStreamSynchronize(s), "ksg");
+  // psi(n) = -gamma + H(n - 1) at integers
+  std::vector<double> H(c + 2, 0.0);
+  for (size_t m = 1; m < H.size(); ++m) H[m] = H[m - 1] + 1.0 / (double)m;
+  const double gamma = 0.57721566490153286061;
+  auto psi = [&](size_t n) { return -gamma + H[n - 1]; };
+  double sum = 0.0;
+  for (size_t i = 0; i < c; ++i) sum += psi((size_t)h[2 * i] + 1) + psi((size_t)h[2 * i + 1] + 1);
+  const double mi = psi(v) + psi(c) - sum / (double)c;
   return mi;
 }
 

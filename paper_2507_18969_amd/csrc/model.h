@@ -8,6 +8,7 @@
 #include "fused.h"
 #include "gemm.h"
 #include "kernels.h"
+#include "memory.h"
 
 namespace edpc {
 
@@ -21,7 +22,6 @@ struct Error {
   std::string msg;
 };
 [[noreturn]] void fail(edpc_status st, const std::string& msg);
-void hip_check(hipError_t e, const char* what);
 
 // Product slots that carry their own tile configuration.
 enum ProductSlot : int {
@@ -194,10 +194,10 @@ struct Model {
     const uint4* nn;
   };
   std::vector<FragMat> frag_mats;
-  std::vector<void*> allocs;
+  Upload tables;  // problem and job tables of build_tables
+  DeviceMemory mem;
 
   Model(const edpc_config& c, size_t n_slots, size_t max_rows, const KernelConfig* kc);
-  ~Model();
   Model(const Model&) = delete;
   Model& operator=(const Model&) = delete;
 
@@ -216,7 +216,7 @@ struct Model {
             hipStream_t s, const StepSched* sched = nullptr);
 
   void product(int ps, int j, int R, hipStream_t s);
-  void setup_fused(hipStream_t s);
+  void setup_fused();
   void autotune(hipStream_t s);
   static KernelConfig default_config(const edpc_config& c, size_t rows);
   // FP32 input of refinement block j (j = N: the head's input) of the last
@@ -225,8 +225,7 @@ struct Model {
   static void validate(const edpc_config& c);
 
  private:
-  template <class T>
-  T* dalloc(size_t n);
+  void allocate();  // parameters, state and workspace
   void gemm(int slot, bool ak, bool bk, EpiKind epi, int nb, GemmArgs g, int grid_rows,
             hipStream_t s);
 };

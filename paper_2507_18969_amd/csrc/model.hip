@@ -230,15 +230,6 @@ KernelConfig Model::default_config(const edpc_config& c, size_t rows) {
   return k;
 }
 
-template <class T>
-T* Model::dalloc(size_t n) {
-  void* p = nullptr;
-  if (n == 0) n = 1;
-  hip_check(hipMalloc(&p, n * sizeof(T)), "hipMalloc");
-  allocs.push_back(p);
-  return (T*)p;
-}
-
 static size_t align64(size_t x) { return (x + 63) & ~(size_t)63; }
 
 Model::Model(const edpc_config& c, size_t nslots, size_t rows, const KernelConfig* kcfg)
@@ -301,81 +292,84 @@ Model::Model(const edpc_config& c, size_t nslots, size_t rows, const KernelConfi
   add("wh", 256 * (size_t)F, zh ? 0 : 7, zh ? 0.0 : bF);
   add("bh", 256, zh ? 0 : 8, zh ? 0.0 : bF);
 
-  param = dalloc<float>(P);
-  grad = dalloc<float>(P);
-  m = dalloc<float>(P);
-  v = dalloc<float>(P);
-  if (bf16) p16 = dalloc<bf16_t>(P);
+  scratch_give_back();
+  mem.place_together([this] { allocate(); });
+}
+
+void Model::allocate() {
+  for (auto* v32 : {&Hs, &Z32, &mean, &rstd, &Abr, &G32, &dA32, &dZ, &dH32}) v32->clear();
+  for (auto* v16 : {&Z16, &G16, &dA16, &dH16}) v16->clear();
+  param = mem.take<float>(P);
+  grad = mem.take<float>(P);
+  m = mem.take<float>(P);
+  v = mem.take<float>(P);
+  if (bf16) p16 = mem.take<bf16_t>(P);
   const size_t fdm = n_slots * (size_t)L * L;
-  U = dalloc<float>(fdm);
-  mU = dalloc<float>(fdm);
-  vU = dalloc<float>(fdm);
+  U = mem.take<float>(fdm);
+  mU = mem.take<float>(fdm);
+  vU = mem.take<float>(fdm);
   if (low_rank) {
     const size_t fac = n_slots * (size_t)F * L;
-    A = dalloc<float>(fac);
-    mA = dalloc<float>(fac);
-    vA = dalloc<float>(fac);
-    B = dalloc<float>(fac);
-    mB = dalloc<float>(fac);
-    vB = dalloc<float>(fac);
+    A = mem.take<float>(fac);
+    mA = mem.take<float>(fac);
+    vA = mem.take<float>(fac);
+    B = mem.take<float>(fac);
+    mB = mem.take<float>(fac);
+    vB = mem.take<float>(fac);
   }
-  st = dalloc<StepState>(1);
+  st = mem.take<StepState>(1);
 
   const size_t R = max_rows;
-  ctx = dalloc<uint8_t>(R * C);
-  tgt = dalloc<uint8_t>(R);
-  slot = dalloc<uint32_t>(R);
+  ctx = mem.take<uint8_t>(R * C);
+  tgt = mem.take<uint8_t>(R);
+  slot = mem.take<uint32_t>(R);
   // without the LTE the FDM reads the FP32 embedding (x' = x) and writes the
   // first block's input (x'' = y) directly
-  if (bf16 && lte) X16 = dalloc<bf16_t>(R * F);
-  if (!bf16 || !lte) X32 = dalloc<float>(R * F);
-  X1 = (lte || low_rank) ? dalloc<float>(R * L) : X32;
-  for (int j = 0; j <= N; ++j) Hs.push_back(dalloc<float>(R * F));
+  if (bf16 && lte) X16 = mem.take<bf16_t>(R * F);
+  if (!bf16 || !lte) X32 = mem.take<float>(R * F);
+  X1 = (lte || low_rank) ? mem.take<float>(R * L) : X32;
+  for (int j = 0; j <= N; ++j) Hs.push_back(mem.take<float>(R * F));
   if (lte) {
-    if (bf16) Y16 = dalloc<bf16_t>(R * L); else Y32 = dalloc<float>(R * L);
+    if (bf16) Y16 = mem.take<bf16_t>(R * L); else Y32 = mem.take<float>(R * L);
   } else if (low_rank) {  // y = x' U_s in FP32, then x'' = y B_s writes the first block's input
-    Y32 = dalloc<float>(R * L);
+    Y32 = mem.take<float>(R * L);
   } else {
     Y32 = Hs[0];
   }
-  if (bf16) HN16 = dalloc<bf16_t>(R * F);
+  if (bf16) HN16 = mem.take<bf16_t>(R * F);
   for (int j = 0; j < N; ++j) {
-    if (bf16) Z16.push_back(dalloc<bf16_t>(R * F)); else Z32.push_back(dalloc<float>(R * F));
-    mean.push_back(dalloc<float>(R));
-    rstd.push_back(dalloc<float>(R));
-    Abr.push_back(dalloc<float>(R * K * H));
-    if (bf16) G16.push_back(dalloc<bf16_t>(R * H)); else G32.push_back(dalloc<float>(R * H));
-    dA32.push_back(dalloc<float>(R * K * H));
-    if (bf16) dA16.push_back(dalloc<bf16_t>(R * K * H));
-    dZ.push_back(dalloc<float>(R * F));
+    if (bf16) Z16.push_back(mem.take<bf16_t>(R * F)); else Z32.push_back(mem.take<float>(R * F));
+    mean.push_back(mem.take<float>(R));
+    rstd.push_back(mem.take<float>(R));
+    Abr.push_back(mem.take<float>(R * K * H));
+    if (bf16) G16.push_back(mem.take<bf16_t>(R * H)); else G32.push_back(mem.take<float>(R * H));
+    dA32.push_back(mem.take<float>(R * K * H));
+    if (bf16) dA16.push_back(mem.take<bf16_t>(R * K * H));
+    dZ.push_back(mem.take<float>(R * F));
   }
   for (int j = 0; j <= N; ++j) {
-    dH32.push_back(dalloc<float>(R * F));
-    if (bf16) dH16.push_back(dalloc<bf16_t>(R * F));
+    dH32.push_back(mem.take<float>(R * F));
+    if (bf16) dH16.push_back(mem.take<bf16_t>(R * F));
   }
-  logits = dalloc<float>(R * 256);
-  dz32 = dalloc<float>(R * 256);
-  if (bf16) dz16 = dalloc<bf16_t>(R * 256);
-  loss_rows = dalloc<float>(R);
-  loss_out = dalloc<float>(1);
-  dX = dalloc<float>(R * F);
+  logits = mem.take<float>(R * 256);
+  dz32 = mem.take<float>(R * 256);
+  if (bf16) dz16 = mem.take<bf16_t>(R * 256);
+  loss_rows = mem.take<float>(R);
+  loss_out = mem.take<float>(1);
+  dX = mem.take<float>(R * F);
   if (lte) {
-    dY = dalloc<float>(R * L);
-    dX1_32 = dalloc<float>(R * L);
-    if (bf16) dX1_16 = dalloc<bf16_t>(R * L);
+    dY = mem.take<float>(R * L);
+    dX1_32 = mem.take<float>(R * L);
+    if (bf16) dX1_16 = mem.take<bf16_t>(R * L);
   } else if (low_rank) {
-    dY = dalloc<float>(R * L);
-    dX1_32 = dalloc<float>(R * L);
+    dY = mem.take<float>(R * L);
+    dX1_32 = mem.take<float>(R * L);
   } else {  // dy = dx'' and dx = dx'
     dY = dH32[0];
     dX1_32 = dX;
   }
   emb_grad_plan((int)R, C, E, &emb_chunk, &emb_sub);
-  emb_partial = dalloc<float>(((R + emb_chunk - 1) / emb_chunk) * 256 * (size_t)E);
-}
-
-Model::~Model() {
-  for (void* p : allocs) (void)hipFree(p);
+  emb_partial = mem.take<float>(((R + emb_chunk - 1) / emb_chunk) * 256 * (size_t)E);
 }
 
 const TensorInfo& Model::tensor(const std::string& name) const {
@@ -390,25 +384,18 @@ const void* Model::W_(const std::string& name) const {
 }
 
 void Model::init_params(hipStream_t s) {
-  hip_check(hipMemsetAsync(param, 0, P * sizeof(float), s), "memset");
-  for (const auto& t : tens) {
-    if (t.tid) k_init_uniform(param + t.off, t.numel, cfg.seed, t.tid, 0, t.bound, s);
-    else k_fill(param + t.off, t.numel, t.bound, s);
-  }
-  k_init_uniform(U, n_slots * (size_t)L * L, cfg.seed, 4, 0,
-                 (float)(1.0 / std::sqrt((double)L)), s);
-  hip_check(hipMemsetAsync(m, 0, P * sizeof(float), s), "memset");
-  hip_check(hipMemsetAsync(v, 0, P * sizeof(float), s), "memset");
-  hip_check(hipMemsetAsync(grad, 0, P * sizeof(float), s), "memset");
-  hip_check(hipMemsetAsync(mU, 0, n_slots * (size_t)L * L * sizeof(float), s), "memset");
-  hip_check(hipMemsetAsync(vU, 0, n_slots * (size_t)L * L * sizeof(float), s), "memset");
-  if (low_rank) {  // slot s draws the counter range starting at s * F * L, like U
+  std::vector<InitTensor> it;
+  for (const auto& t : tens) it.push_back(InitTensor{t.off, t.numel, t.tid, t.bound});
+  k_init_shared(it.data(), (int)it.size(), P, cfg.seed, param, m, v, grad, bf16 ? p16 : nullptr, s);
+  // slot s of a per-stream matrix draws the counter range starting at s times
+  // the matrix's size
+  const size_t fdm = n_slots * (size_t)L * L;
+  k_init_streams(U, mU, vU, fdm, cfg.seed, 4, (float)(1.0 / std::sqrt((double)L)), s);
+  if (low_rank) {
     const size_t fac = n_slots * (size_t)F * L;
-    k_init_uniform(A, fac, cfg.seed, 9, 0, (float)(1.0 / std::sqrt((double)F)), s);
-    k_init_uniform(B, fac, cfg.seed, 10, 0, (float)(1.0 / std::sqrt((double)L)), s);
-    for (float* z : {mA, vA, mB, vB}) hip_check(hipMemsetAsync(z, 0, fac * sizeof(float), s), "memset");
+    k_init_streams(A, mA, vA, fac, cfg.seed, 9, (float)(1.0 / std::sqrt((double)F)), s);
+    k_init_streams(B, mB, vB, fac, cfg.seed, 10, (float)(1.0 / std::sqrt((double)L)), s);
   }
-  if (bf16) k_to_bf16(param, p16, P, s);
   if (kc.fused) build_frags(s);
   hip_check(hipGetLastError(), "init");
   tau = 0;
@@ -452,16 +439,14 @@ void Model::build_tables(hipStream_t s) {
     t.n = (int)wg.size();
     t.tiles = tiles;
     t.host = wg;
-    t.d = dalloc<WgradProblem>(wg.size());
-    hip_check(hipMemcpyAsync(t.d, wg.data(), wg.size() * sizeof(WgradProblem),
-                             hipMemcpyHostToDevice, s), "copy");
+    tables.add(&t.d, wg);
   }
 
   // scratch of the balanced weight-gradient launch (wide tiles, large tables)
   if (bf16 && kc.tile[PS_WGRAD] >= TILE_W128x128 &&
       wg_tab[kc.tile[PS_WGRAD]].tiles >= kWgradRanges) {
     wg_part_floats = wgrad_part_floats(kc.tile[PS_WGRAD]);
-    wg_part = dalloc<float>(wg_part_floats);
+    wg_part = mem.take<float>(wg_part_floats);
   }
 
   // column sums: bias gradients, LayerNorm affine gradients.  Where the
@@ -504,7 +489,7 @@ void Model::build_tables(hipStream_t s) {
   ln_part.assign(fold ? N : 0, nullptr);
   if (fold) {
     for (int j = 0; j < N; ++j) {
-      ln_part[j] = dalloc<float>(ln_fold_part_elems((int)max_rows, F));
+      ln_part[j] = mem.take<float>(ln_fold_part_elems((int)max_rows, F));
       const std::string b = "blk" + std::to_string(j), ln = "ln" + std::to_string(j);
       float* dsts[3] = {G_(ln + ".beta"), G_(ln + ".gamma"), G_(b + ".bo")};
       for (int q = 0; q < 3; ++q) {
@@ -523,10 +508,8 @@ void Model::build_tables(hipStream_t s) {
     }
   }
   n_cs = (int)cs.size();
-  d_cs = dalloc<ColsumJob>(cs.size());
-  cs_partial = dalloc<float>(colsum_partial_elems((int)max_rows, cs_cols));
-  hip_check(hipMemcpyAsync(d_cs, cs.data(), cs.size() * sizeof(ColsumJob), hipMemcpyHostToDevice, s),
-            "copy");
+  tables.add(&d_cs, cs);
+  cs_partial = mem.take<float>(colsum_partial_elems((int)max_rows, cs_cols));
   ColsumJob lj{};
   lj.src = loss_rows;
   lj.h = nullptr;
@@ -537,14 +520,14 @@ void Model::build_tables(hipStream_t s) {
   lj.col_block_begin = 0;
   lj.col_offset = 0;
   lj.scale = 0.0f;  // scale by 1/rows
-  loss_partial = dalloc<float>(colsum_partial_elems((int)max_rows, 1));
-  d_loss_job = dalloc<ColsumJob>(1);
-  hip_check(hipMemcpyAsync(d_loss_job, &lj, sizeof(lj), hipMemcpyHostToDevice, s), "copy");
-  if (kc.fused) setup_fused(s);
-  hip_check(hipStreamSynchronize(s), "sync");
+  loss_partial = mem.take<float>(colsum_partial_elems((int)max_rows, 1));
+  tables.add(&d_loss_job, &lj, 1);
+  if (kc.fused) setup_fused();
+  tables.commit(mem, s);
+  if (kc.fused) build_frags(s);
 }
 
-void Model::setup_fused(hipStream_t s) {
+void Model::setup_fused() {
   // fragment-ordered BF16 copies of every matrix the row-block kernel streams
   struct Mat { const char* name; int rows, cols; };
   std::vector<FragJob> jobs;
@@ -571,7 +554,7 @@ void Model::setup_fused(hipStream_t s) {
     add("blk" + std::to_string(j) + ".wo", F, H);
   }
   add("wh", 256, F);
-  frags = dalloc<uint4>(off);
+  frags = mem.take<uint4>(off);
   for (auto& j : jobs) {
     j.nt = frags + (size_t)j.nt;
     j.nn = frags + (size_t)j.nn;
@@ -622,9 +605,7 @@ void Model::setup_fused(hipStream_t s) {
     n_adam_jobs = (int)aj.size();
     adam_items = items;
   }
-  d_frag_jobs = dalloc<FragJob>(jobs.size());
-  hip_check(hipMemcpyAsync(d_frag_jobs, jobs.data(), jobs.size() * sizeof(FragJob),
-                           hipMemcpyHostToDevice, s), "copy");
+  tables.add(&d_frag_jobs, jobs);
   auto nt = [&](const std::string& n) -> const uint4* {
     for (auto& w : where) if (w.first == n) return frags + w.second;
     fail(EDPC_E_DEVICE, "fragment table");
@@ -694,11 +675,9 @@ void Model::setup_fused(hipStream_t s) {
   fcs_cols = cols;
   n_fcs = (int)cs.size();
   fa.colpart_cols = cols;
-  fused_colpart = dalloc<float>(((max_rows + kFusedRows - 1) / kFusedRows) * (size_t)cols);
+  fused_colpart = mem.take<float>(((max_rows + kFusedRows - 1) / kFusedRows) * (size_t)cols);
   fa.colpart = fused_colpart;
-  d_fcs = dalloc<ColsumJob>(cs.size());
-  hip_check(hipMemcpyAsync(d_fcs, cs.data(), cs.size() * sizeof(ColsumJob), hipMemcpyHostToDevice, s),
-            "copy");
+  tables.add(&d_fcs, cs);
   std::memset(&fin, 0, sizeof(fin));
   fin.st = st;
   fin.C = C;
@@ -718,7 +697,7 @@ void Model::setup_fused(hipStream_t s) {
   fout.dx1_16 = dX1_16;
   fout.dx1_32 = dX1_32;
   fout.ctx = ctx;
-  fused_emb_partial = dalloc<float>(((max_rows + kFusedRows - 1) / kFusedRows) * 256 * (size_t)E);
+  fused_emb_partial = mem.take<float>(((max_rows + kFusedRows - 1) / kFusedRows) * 256 * (size_t)E);
   fout.emb_partial = fused_emb_partial;
   fout.colpart = fused_colpart;
   // element-range Adam jobs take their gradients from the row-block partials
@@ -737,9 +716,7 @@ void Model::setup_fused(hipStream_t s) {
       }
     if (!aj[k].red) fail(EDPC_E_DEVICE, "no gradient partials for " + aj_name[k]);
   }
-  d_adam_jobs = dalloc<AdamJob>(aj.size());
-  hip_check(hipMemcpyAsync(d_adam_jobs, aj.data(), aj.size() * sizeof(AdamJob),
-                           hipMemcpyHostToDevice, s), "copy");
+  tables.add(&d_adam_jobs, aj);
   {  // the element-range jobs alone, and weight-gradient tables that apply Adam
     std::vector<AdamJob> ae;
     int items = 0;
@@ -751,9 +728,7 @@ void Model::setup_fused(hipStream_t s) {
     }
     n_adam_elem_jobs = (int)ae.size();
     adam_elem_items = items;
-    d_adam_elem_jobs = dalloc<AdamJob>(ae.size());
-    hip_check(hipMemcpyAsync(d_adam_elem_jobs, ae.data(), ae.size() * sizeof(AdamJob),
-                             hipMemcpyHostToDevice, s), "copy");
+    tables.add(&d_adam_elem_jobs, ae);
     for (int tile = 0; tile < TILE_W128x128; ++tile) {
       std::vector<WgradProblem> wp = wg_tab[tile].host;
       bool ok = !wp.empty();
@@ -767,14 +742,11 @@ void Model::setup_fused(hipStream_t s) {
         if (!p.nt || p.M % 32 || p.N % 32) ok = false;
       }
       if (!ok) continue;
-      wg_tab[tile].d_adam = dalloc<WgradProblem>(wp.size());
-      hip_check(hipMemcpyAsync(wg_tab[tile].d_adam, wp.data(), wp.size() * sizeof(WgradProblem),
-                               hipMemcpyHostToDevice, s), "copy");
+      tables.add(&wg_tab[tile].d_adam, wp);
     }
   }
   fout.colpart_cols = cols;
   fout.off_b1 = off_b1;
-  build_frags(s);
 }
 
 void Model::gemm(int ps, bool ak, bool bk, EpiKind epi, int nb, GemmArgs g, int grid_rows,
@@ -1055,7 +1027,7 @@ void Model::autotune(hipStream_t s) {
       wg_tab[kc.tile[PS_WGRAD]].tiles >= kWgradRanges &&
       wgrad_part_floats(kc.tile[PS_WGRAD]) > wg_part_floats) {
     wg_part_floats = wgrad_part_floats(kc.tile[PS_WGRAD]);
-    wg_part = dalloc<float>(wg_part_floats);
+    wg_part = mem.take<float>(wg_part_floats);
   }
   timer = saved;
   (void)hipEventDestroy(e0);

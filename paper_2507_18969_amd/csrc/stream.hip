@@ -122,7 +122,7 @@ size_t stream_encode(const edpc_config& cfg, const uint8_t* h_in, const uint64_t
   ss->n = n;
   ss->lens.assign(lens, lens + n);
   common_setup(*ss, nullptr);
-  uint8_t* window = ss->dalloc<uint8_t>(n * W);
+  uint8_t* window = ss->mem.take<uint8_t>(n * W);
   use_window(*ss, window, W);
   std::vector<uint64_t> in_off(n), pay_off(n), pay_cap(n);
   uint64_t o = 0, po = 0;
@@ -133,12 +133,11 @@ size_t stream_encode(const edpc_config& cfg, const uint8_t* h_in, const uint64_t
     pay_cap[i] = 2 * lens[i] + 8;
     po += pay_cap[i];
   }
-  ss->d_pay = ss->dalloc<uint8_t>(po);
-  ss->d_pay_off = ss->dalloc<uint64_t>(n);
-  ss->d_pay_cap = ss->dalloc<uint64_t>(n);
-  hip_check(hipMemcpyAsync(ss->d_pay_off, pay_off.data(), n * 8, hipMemcpyHostToDevice, s), "copy");
-  hip_check(hipMemcpyAsync(ss->d_pay_cap, pay_cap.data(), n * 8, hipMemcpyHostToDevice, s), "copy");
-  ss->d_enc = ss->dalloc<RcEnc>(n);
+  ss->d_pay = ss->mem.take<uint8_t>(po);
+  ss->tables.add(&ss->d_pay_off, pay_off);
+  ss->tables.add(&ss->d_pay_cap, pay_cap);
+  ss->tables.commit(ss->mem, s);
+  ss->d_enc = ss->mem.take<RcEnc>(n);
   ss->io.src = window;
   ss->io.pay = ss->d_pay;
   ss->io.pay_off = ss->d_pay_off;
@@ -148,10 +147,10 @@ size_t stream_encode(const edpc_config& cfg, const uint8_t* h_in, const uint64_t
   // drained payload bytes: at most 2 per step per stream plus the bytes a
   // run of 0xFF held back; the drain takes at most `stride` at a time
   const uint32_t stride = 2 * T + 64;
-  uint64_t* d_done = ss->dalloc<uint64_t>(n);
+  uint64_t* d_done = ss->mem.take<uint64_t>(n);
   hip_check(hipMemsetAsync(d_done, 0, n * 8, s), "memset");
-  uint8_t* d_drain[2] = {ss->dalloc<uint8_t>(n * (size_t)stride), ss->dalloc<uint8_t>(n * (size_t)stride)};
-  uint32_t* d_dlen[2] = {ss->dalloc<uint32_t>(n), ss->dalloc<uint32_t>(n)};
+  uint8_t* d_drain[2] = {ss->mem.take<uint8_t>(n * (size_t)stride), ss->mem.take<uint8_t>(n * (size_t)stride)};
+  uint32_t* d_dlen[2] = {ss->mem.take<uint32_t>(n), ss->mem.take<uint32_t>(n)};
   Pinned in_stage0(n * (size_t)T), in_stage1(n * (size_t)T);
   uint8_t* in_stage[2] = {in_stage0.p, in_stage1.p};
   Pinned h_drain0(n * (size_t)stride + n * 4), h_drain1(n * (size_t)stride + n * 4);
@@ -292,10 +291,10 @@ size_t stream_decode(const uint8_t* h_in, size_t in_len, uint8_t* h_out, size_t 
   ss->lens = h.lens;
   ss->hdr = h;
   common_setup(*ss, &kc);
-  uint8_t* window = ss->dalloc<uint8_t>(n * W);
+  uint8_t* window = ss->mem.take<uint8_t>(n * W);
   use_window(*ss, window, W);
   // the payloads go up once (they are what the decoder reads first)
-  uint8_t* d_pay = ss->dalloc<uint8_t>(h.total_pay);
+  uint8_t* d_pay = ss->mem.take<uint8_t>(h.total_pay);
   if (h.total_pay)
     hip_check(hipMemcpyAsync(d_pay, h_in + h.header_len, h.total_pay, hipMemcpyHostToDevice, s), "copy");
   std::vector<uint64_t> pay_off(n), out_off(n);
@@ -306,11 +305,10 @@ size_t stream_decode(const uint8_t* h_in, size_t in_len, uint8_t* h_out, size_t 
     out_off[i] = o;
     o += h.lens[i];
   }
-  ss->d_pay_off = ss->dalloc<uint64_t>(n);
-  ss->d_pay_cap = ss->dalloc<uint64_t>(n);
-  hip_check(hipMemcpyAsync(ss->d_pay_off, pay_off.data(), n * 8, hipMemcpyHostToDevice, s), "copy");
-  hip_check(hipMemcpyAsync(ss->d_pay_cap, h.pay_lens.data(), n * 8, hipMemcpyHostToDevice, s), "copy");
-  ss->d_dec = ss->dalloc<RcDec>(n);
+  ss->tables.add(&ss->d_pay_off, pay_off);
+  ss->tables.add(&ss->d_pay_cap, h.pay_lens);
+  ss->tables.commit(ss->mem, s);
+  ss->d_dec = ss->mem.take<RcDec>(n);
   ss->io.dst = window;
   ss->io.pay_in = d_pay;
   ss->io.pay_off = ss->d_pay_off;
