@@ -346,9 +346,6 @@ edpc_status edpc_model_step(edpc_model* mh, const uint8_t* d_ctx, const uint8_t*
       seen[h_slot[r]] = 1;
     }
     hipStream_t s = S(stream);
-    hip_check(hipMemcpyAsync(m.ctx, d_ctx, rows * m.C, hipMemcpyDeviceToDevice, s), "copy");
-    if (d_target) hip_check(hipMemcpyAsync(m.tgt, d_target, rows, hipMemcpyDeviceToDevice, s), "copy");
-    hip_check(hipMemcpyAsync(m.slot, h_slot, rows * sizeof(uint32_t), hipMemcpyHostToDevice, s), "copy");
     StepOutputs out;
     out.probs = d_probs;
     out.cum = d_cum;
@@ -360,7 +357,16 @@ edpc_status edpc_model_step(edpc_model* mh, const uint8_t* d_ctx, const uint8_t*
     if (out.keep_fdm_grad)  // slots outside this call get a zero gradient
       hip_check(hipMemsetAsync(m.dUkeep, 0, m.n_slots * (size_t)m.L * m.L * sizeof(float), s), "memset");
     const uint32_t tau = out.update ? (uint32_t)(m.tau + 1) : (uint32_t)(m.tau > 0 ? m.tau : 1);
-    k_step_explicit(m.st, (int)rows, tau, m.cfg.beta1, m.cfg.beta2, s);
+    if (rows <= (size_t)kInlineSlots) {
+      InlineSlots in;
+      std::memcpy(in.v, h_slot, rows * sizeof(uint32_t));
+      k_stage(m.st, (int)rows, tau, m.cfg.beta1, m.cfg.beta2, d_ctx, m.ctx, m.C, d_target, m.tgt, in, m.slot, s);
+    } else {
+      hip_check(hipMemcpyAsync(m.ctx, d_ctx, rows * m.C, hipMemcpyDeviceToDevice, s), "copy");
+      if (d_target) hip_check(hipMemcpyAsync(m.tgt, d_target, rows, hipMemcpyDeviceToDevice, s), "copy");
+      hip_check(hipMemcpyAsync(m.slot, h_slot, rows * sizeof(uint32_t), hipMemcpyHostToDevice, s), "copy");
+      k_step_explicit(m.st, (int)rows, tau, m.cfg.beta1, m.cfg.beta2, s);
+    }
     StreamIO io;
     std::memset(&io, 0, sizeof(io));
     io.slot = m.slot;

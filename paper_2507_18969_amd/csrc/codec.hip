@@ -162,22 +162,11 @@ uint64_t Session::bucket_end(int rows) const {
 }
 
 void Session::step_direct(uint64_t i, int grid_rows, bool explicit_step, hipStream_t st, int rel) {
-  KTimer* timer = model->timer;
   StepOutputs out;
   out.update = true;
-  if (model->kc.fused) {
-    // the row-block step's first kernel forms the step state
-    const StepSched sc{sched, explicit_step ? 1 : 2, explicit_step ? (int)i : rel};
-    model->step(decoding ? MODE_DECODE : MODE_ENCODE, io, out, grid_rows, st, &sc);
-    return;
-  }
-  if (timer) timer->begin(KC_SCHEDULE, st);
-  k_step_schedule(model->st, sched, explicit_step ? (int)i : -1, st);
-  if (timer) timer->end(st);
-  if (timer) timer->begin(KC_GATHER, st);
-  k_gather(model->st, io, model->C, model->ctx, model->tgt, grid_rows, decoding, st);
-  if (timer) timer->end(st);
-  model->step(decoding ? MODE_DECODE : MODE_ENCODE, io, out, grid_rows, st);
+  // the step's first kernel forms the step state
+  const StepSched sc{sched, explicit_step ? 1 : 2, explicit_step ? (int)i : rel};
+  model->step(decoding ? MODE_DECODE : MODE_ENCODE, io, out, grid_rows, st, &sc);
 }
 
 // Steps next .. next+k-1.  Windows of graph_steps steps whose active rows fall

@@ -80,14 +80,23 @@ __device__ inline void write_step_state(StepState* st, const Schedule& sc, int s
   st->bc2 = adam_bias_correction(sc.beta2, tau);
 }
 
-// step >= 0: state for that step; step < 0: the step after st->step.
-void k_step_schedule(StepState* st, Schedule sc, int step, hipStream_t s);
 // st->step = st->base = step (the step before a window of relative steps)
 void k_step_set(StepState* st, int step, hipStream_t s);
 void k_step_explicit(StepState* st, int rows, uint32_t tau, float beta1, float beta2, hipStream_t s);
 
-void k_gather(const StepState* st, StreamIO io, int C, uint8_t* ctx, uint8_t* tgt, int max_rows,
-              bool decoding, hipStream_t s);
+// A step on explicit contexts, staged in one launch for at most kInlineSlots rows.
+constexpr int kInlineSlots = 768;
+struct InlineSlots {
+  uint32_t v[kInlineSlots];
+};
+void k_stage(StepState* st, int rows, uint32_t tau, float beta1, float beta2, const uint8_t* src_ctx,
+             uint8_t* ctx, int C, const uint8_t* src_tgt, uint8_t* tgt, const InlineSlots& slots,
+             uint32_t* slot, hipStream_t s);
+// State, gather and embedding of a coding step; mode 1: step `step`, mode 2:
+// step st->base + step.  max_rows <= sc.n.
+void k_embed_streams(StepState* st, const Schedule& sc, int mode, int step, const StreamIO& io, int C,
+                     int E, bool decoding, const float* emb, uint8_t* ctx, uint8_t* tgt, float* x32,
+                     bf16_t* x16, int max_rows, hipStream_t s);
 void k_embed(const StepState* st, const uint8_t* ctx, const float* emb, int C, int E, float* x32,
              bf16_t* x16, int max_rows, hipStream_t s);
 // Per-stream [Lin, Lout] matrix: Lin <= 256, Lout a power of two in 4..256.

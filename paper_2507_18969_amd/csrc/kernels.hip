@@ -11,25 +11,6 @@ static inline unsigned blocks_for(size_t n, unsigned per) { return (unsigned)((n
 // ---------------------------------------------------------------------------
 // Step state
 // ---------------------------------------------------------------------------
-// rows = number of streams with length > step (lens sorted decreasing).  A
-// 256-way search: each round every thread tests one of 256 evenly spaced
-// positions of the open range and the count of true tests narrows the range to
-// one gap between positions, so n streams take ceil(log_256 n) rounds of one
-// load each instead of log_2 n dependent loads.
-constexpr int kScheduleThreads = 256;
-
-__global__ void __launch_bounds__(kScheduleThreads) step_schedule_kernel(StepState* st, Schedule sc,
-                                                                         int step) {
-  if (step < 0) step = st->step + 1;
-  const int rows = active_rows(sc, step);
-  __syncthreads();  // every thread has read st->step
-  if (threadIdx.x == 0) write_step_state(st, sc, step, rows);
-}
-
-void k_step_schedule(StepState* st, Schedule sc, int step, hipStream_t s) {
-  hipLaunchKernelGGL(step_schedule_kernel, dim3(1), dim3(kScheduleThreads), 0, s, st, sc, step);
-}
-
 __global__ void step_set_kernel(StepState* st, int step) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     st->step = step;
@@ -41,9 +22,8 @@ void k_step_set(StepState* st, int step, hipStream_t s) {
   hipLaunchKernelGGL(step_set_kernel, dim3(1), dim3(64), 0, s, st, step);
 }
 
-__global__ void step_explicit_kernel(StepState* st, int rows, uint32_t tau, float beta1,
-                                     float beta2) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__device__ __forceinline__ void explicit_state(StepState* st, int rows, uint32_t tau, float beta1,
+                                              float beta2) {
   st->step = -1;
   st->rows = rows;
   st->inv_rows = rows > 0 ? 1.0f / (float)rows : 0.0f;
@@ -51,6 +31,11 @@ __global__ void step_explicit_kernel(StepState* st, int rows, uint32_t tau, floa
   st->tau = tau;
   st->bc1 = adam_bias_correction(beta1, tau);
   st->bc2 = adam_bias_correction(beta2, tau);
+}
+
+__global__ void step_explicit_kernel(StepState* st, int rows, uint32_t tau, float beta1,
+                                     float beta2) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) explicit_state(st, rows, tau, beta1, beta2);
 }
 
 void k_step_explicit(StepState* st, int rows, uint32_t tau, float beta1, float beta2,
@@ -61,50 +46,98 @@ void k_step_explicit(StepState* st, int rows, uint32_t tau, float beta1, float b
 // ---------------------------------------------------------------------------
 // Context window gather and byte embedding
 // ---------------------------------------------------------------------------
-__global__ void gather_kernel(const StepState* __restrict__ st, StreamIO io, int C,
-                              uint8_t* __restrict__ ctx, uint8_t* __restrict__ tgt,
-                              bool decoding) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = idx / C, c = idx % C;
-  if (r >= st->rows) return;
-  const int i = st->step;
-  const uint32_t s = io.slot[r];
-  const uint8_t* base = decoding ? io.dst : io.src;
-  const uint64_t o = io.off[s];
-  ctx[idx] = base[io_at(io, o, (uint64_t)(i - C + c))];
-  if (!decoding && c == 0) tgt[r] = io.src[io_at(io, o, (uint64_t)i)];
-}
-
-void k_gather(const StepState* st, StreamIO io, int C, uint8_t* ctx, uint8_t* tgt, int max_rows,
-              bool decoding, hipStream_t s) {
-  const size_t n = (size_t)max_rows * C;
-  hipLaunchKernelGGL(gather_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, st, io, C, ctx, tgt,
-                     decoding);
-}
-
-__global__ void embed_kernel(const StepState* __restrict__ st, const uint8_t* __restrict__ ctx,
-                             const float* __restrict__ emb, int C, int E, float* __restrict__ x32,
-                             bf16_t* __restrict__ x16) {
-  const int F = C * E;
-  const int q4 = F >> 2;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = idx / q4, f = (idx % q4) * 4;
-  if (r >= st->rows) return;
-  const int c = f / E, e = f % E;
-  const int v = ctx[r * C + c];
-  const float4 val = *(const float4*)(emb + v * E + e);
-  if (x32) *(float4*)(x32 + (size_t)r * F + f) = val;
-  if (x16) {
-    ushort4 h = make_ushort4(f2bf(val.x), f2bf(val.y), f2bf(val.z), f2bf(val.w));
-    *(ushort4*)(x16 + (size_t)r * F + f) = h;
+// X[r][c E + e] = Emb[byte c of row r's context][e]; thread t of 256.
+__device__ __forceinline__ void embed_row(const uint8_t* bytes, const float* __restrict__ emb, int F, int E,
+                                          float* __restrict__ x32, bf16_t* __restrict__ x16, size_t r) {
+  for (int f = 4 * threadIdx.x; f < F; f += 1024) {
+    const int c = f / E, e = f - c * E;
+    const float4 val = *(const float4*)(emb + bytes[c] * E + e);
+    if (x32) *(float4*)(x32 + r * F + f) = val;
+    if (x16)
+      *(ushort4*)(x16 + r * F + f) = make_ushort4(f2bf(val.x), f2bf(val.y), f2bf(val.z), f2bf(val.w));
   }
+}
+
+// One workgroup per row.
+__global__ void __launch_bounds__(256) embed_kernel(const StepState* __restrict__ st,
+                                                    const uint8_t* __restrict__ ctx,
+                                                    const float* __restrict__ emb, int C, int E,
+                                                    float* __restrict__ x32, bf16_t* __restrict__ x16) {
+  const int r = blockIdx.x;
+  if (r >= st->rows) return;
+  embed_row(ctx + (size_t)r * C, emb, C * E, E, x32, x16, r);
 }
 
 void k_embed(const StepState* st, const uint8_t* ctx, const float* emb, int C, int E, float* x32,
              bf16_t* x16, int max_rows, hipStream_t s) {
-  const size_t n = (size_t)max_rows * C * E / 4;
-  hipLaunchKernelGGL(embed_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, st, ctx, emb, C, E,
-                     x32, x16);
+  hipLaunchKernelGGL(embed_kernel, dim3(max_rows), dim3(256), 0, s, st, ctx, emb, C, E, x32, x16);
+}
+
+// First launch of a coding step of the layer-by-layer sequence: the step state
+// (formed and written by the first workgroup; no other reads it here: a row is
+// active if its own stream is long enough), the row's context and target from
+// its stream, and the embedding.  As launches of their own the three took 6.7 us
+// of a 116 us step of 8 streams, this one 3.8.
+__global__ void __launch_bounds__(256) embed_streams_kernel(StepState* st, Schedule sc, int mode, int step,
+                                                            StreamIO io, int C, int E, bool decoding,
+                                                            const float* __restrict__ emb,
+                                                            uint8_t* __restrict__ ctx,
+                                                            uint8_t* __restrict__ tgt,
+                                                            float* __restrict__ x32,
+                                                            bf16_t* __restrict__ x16) {
+  __shared__ uint8_t bytes[256];
+  if (mode == 2) step += st->base;
+  const int r = blockIdx.x;
+  const uint32_t s = io.slot[r];
+  const bool live = sc.lens_sorted[r] > (int64_t)step;
+  if (live) {
+    const uint8_t* base = decoding ? io.dst : io.src;
+    const uint64_t o = io.off[s];
+    const int c = threadIdx.x;
+    if (c < C) {
+      const uint8_t v = base[io_at(io, o, (uint64_t)(step - C + c))];
+      bytes[c] = v;
+      ctx[(size_t)r * C + c] = v;
+    }
+    if (!decoding && c == 0) tgt[r] = io.src[io_at(io, o, (uint64_t)step)];
+    __syncthreads();
+    embed_row(bytes, emb, C * E, E, x32, x16, r);
+  }
+  if (r == 0) {
+    const int rows = active_rows(sc, step);
+    if (threadIdx.x == 0) write_step_state(st, sc, step, rows);
+  }
+}
+
+void k_embed_streams(StepState* st, const Schedule& sc, int mode, int step, const StreamIO& io, int C,
+                     int E, bool decoding, const float* emb, uint8_t* ctx, uint8_t* tgt, float* x32,
+                     bf16_t* x16, int max_rows, hipStream_t s) {
+  hipLaunchKernelGGL(embed_streams_kernel, dim3(max_rows), dim3(256), 0, s, st, sc, mode, step, io, C, E,
+                     decoding, emb, ctx, tgt, x32, x16);
+}
+
+// Inputs of a step on explicit contexts in one launch: the step state, contexts
+// and targets, and the slots, which come as kernel arguments (three copies and a
+// launch otherwise, the one of the slots from host memory).
+__global__ void __launch_bounds__(256) stage_kernel(StepState* st, int rows, uint32_t tau, float beta1,
+                                                    float beta2, const uint8_t* __restrict__ src_ctx,
+                                                    uint8_t* __restrict__ ctx, int n_ctx,
+                                                    const uint8_t* __restrict__ src_tgt,
+                                                    uint8_t* __restrict__ tgt, InlineSlots slots,
+                                                    uint32_t* __restrict__ slot) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n_ctx) ctx[i] = src_ctx[i];
+  if (i >= rows) return;
+  if (src_tgt) tgt[i] = src_tgt[i];
+  slot[i] = slots.v[i];
+  if (i == 0) explicit_state(st, rows, tau, beta1, beta2);
+}
+
+void k_stage(StepState* st, int rows, uint32_t tau, float beta1, float beta2, const uint8_t* src_ctx,
+             uint8_t* ctx, int C, const uint8_t* src_tgt, uint8_t* tgt, const InlineSlots& slots,
+             uint32_t* slot, hipStream_t s) {
+  hipLaunchKernelGGL(stage_kernel, dim3(blocks_for((size_t)rows * C, 256)), dim3(256), 0, s, st, rows, tau,
+                     beta1, beta2, src_ctx, ctx, rows * C, src_tgt, tgt, slots, slot);
 }
 
 // 16-byte accesses, streaming (non-temporal) where NT.

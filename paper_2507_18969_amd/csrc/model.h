@@ -210,8 +210,8 @@ struct Model {
   void build_tables(hipStream_t s);
   // One step on rows already staged in ctx/tgt/slot with st set; grid_rows
   // bounds the launch grids (>= st->rows).
-  // sched: when given, the row-block step's first kernel sets the step state
-  // itself (see FusedInArgs); other steps take it as already set.
+  // sched: when given (coding steps), the first kernel sets the step state and
+  // gathers the contexts itself; without it both are taken as already set.
   void step(StepMode mode, const StreamIO& io, const StepOutputs& out, int grid_rows,
             hipStream_t s, const StepSched* sched = nullptr);
 

@@ -908,7 +908,11 @@ void Model::step(StepMode mode, const StreamIO& io, const StepOutputs& out, int 
     hip_check(hipGetLastError(), "step launch");
     return;
   }
-  TIMED(KC_EMBED, k_embed(st, ctx, P_("emb"), C, E, X32, X16, R, s));
+  if (sched)  // a coding step: step state, context gather and embedding
+    TIMED(KC_EMBED, k_embed_streams(st, sched->sc, sched->mode, sched->step, io, C, E,
+                                    mode == MODE_DECODE, P_("emb"), ctx, tgt, X32, X16, R, s));
+  else
+    TIMED(KC_EMBED, k_embed(st, ctx, P_("emb"), C, E, X32, X16, R, s));
   if (lte) product(PS_LTE_DOWN, 0, R, s);
   if (low_rank) TIMED(KC_FDM_FWD, k_fdm_fwd(st, X32, A, slot, F, L, X1, nullptr, R, s));  // x' = x A_s
   TIMED(KC_FDM_FWD, k_fdm_fwd(st, X1, U, slot, L, L, Y32, Y16, R, s));  // Eq. 15
