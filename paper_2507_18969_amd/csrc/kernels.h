@@ -138,9 +138,14 @@ struct ColsumJob {
   const float* part;
   int part_ld, part_rows;
 };
+constexpr int kColChunk = 64;  // rows per partial sum of the first pass
 size_t colsum_partial_elems(int max_rows, int total_cols);
 void k_colsum(const StepState* st, const ColsumJob* jobs, int n_jobs, int total_blocks,
               int total_cols, float* partial, int max_rows, hipStream_t s);
+
+// First pass only.
+void k_colsum_partial(const StepState* st, const ColsumJob* jobs, int n_jobs, int total_blocks,
+                      int total_cols, float* partial, int max_rows, hipStream_t s);
 
 // Second pass only: partial[k][col] over chunks of chunk_rows rows.
 void k_colsum_reduce(const StepState* st, const ColsumJob* jobs, int n_jobs, int total_cols,
@@ -151,11 +156,19 @@ void k_emb_grad_reduce(const StepState* st, const float* partial, int chunk_rows
                        float* demb, hipStream_t s);
 
 void emb_grad_plan(int max_rows, int C, int E, int* chunk_rows, int* sub_rows);
-void k_emb_grad(const StepState* st, const uint8_t* ctx, const float* dx, int C, int E,
-                float* partial, int chunk_rows, int sub_rows, int max_rows, float* demb,
-                hipStream_t s);
-void k_adam(const StepState* st, float* p, const float* g, float* m, float* v, bf16_t* p16,
-            size_t n, AdamCfg ac, hipStream_t s);
+void k_emb_grad_partial(const StepState* st, const uint8_t* ctx, const float* dx, int C, int E,
+                        float* partial, int chunk_rows, int sub_rows, int max_rows, hipStream_t s);
+// Gradient of `cols` elements at offset off of the flat buffers: the in-order
+// sum of part[k * ld + e] over the ceil(rows / part_rows) partials.
+struct PartialJob {
+  size_t off;
+  const float* part;
+  int cols, ld, part_rows;
+};
+// Adam on n parameters (a multiple of 64), with the gradients of the job kinds
+// summed on the way; kind[i / 64] = 0 or 1 + the job of element i.
+void k_adam(const StepState* st, float* p, float* g, float* m, float* v, bf16_t* p16, size_t n,
+            AdamCfg ac, const uint8_t* kind, const PartialJob* jobs, hipStream_t s);
 
 // Counter-based initialisation: element j of a tensor is fl32(a_j * bound), a_j
 // from SplitMix64(seed + (tid << 40) + j); tid 0: every element is `bound`.

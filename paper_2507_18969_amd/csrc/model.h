@@ -160,6 +160,8 @@ struct Model {
   ColsumJob* d_cs = nullptr;
   int n_cs = 0, cs_blocks = 0, cs_cols = 0;
   float* cs_partial = nullptr;
+  PartialJob* d_part_jobs = nullptr;  // layer-by-layer Adam: sums formed on the way, and which
+  uint8_t* d_kind = nullptr;          // elements take them
   std::vector<float*> ln_part;  // LayerNorm adjoint's row-group column sums, per block (or empty)
   ColsumJob* d_loss_job = nullptr;
   float* loss_partial = nullptr;

@@ -3,6 +3,7 @@
 #include "model.h"
 #include "trace.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -510,6 +511,22 @@ void Model::build_tables(hipStream_t s) {
   n_cs = (int)cs.size();
   tables.add(&d_cs, cs);
   cs_partial = mem.take<float>(colsum_partial_elems((int)max_rows, cs_cols));
+  if (!kc.fused) {  // where Adam sums a tensor's partials itself
+    std::vector<PartialJob> pj;
+    std::vector<uint8_t> kind(P / 64, 0);
+    auto addp = [&](size_t off, int cols, const float* part, int ld, int part_rows) {
+      pj.push_back(PartialJob{off, part, cols, ld, part_rows});
+      if (pj.size() > 255 || off % 64) fail(EDPC_E_DEVICE, "gradient partial table");
+      std::fill(kind.begin() + off / 64, kind.begin() + (off + cols + 63) / 64, (uint8_t)pj.size());
+    };
+    addp(tensor("emb").off, 256 * E, emb_partial, 256 * E, emb_chunk);
+    for (const ColsumJob& j : cs) {
+      if (j.part) addp((size_t)(j.dst - grad), j.cols, j.part, j.part_ld, j.part_rows);
+      else addp((size_t)(j.dst - grad), j.cols, cs_partial + j.col_offset, cs_cols, kColChunk);
+    }
+    tables.add(&d_part_jobs, pj);
+    tables.add(&d_kind, kind);
+  }
   ColsumJob lj{};
   lj.src = loss_rows;
   lj.h = nullptr;
@@ -957,10 +974,15 @@ void Model::step(StepMode mode, const StreamIO& io, const StepOutputs& out, int 
   if (low_rank)
     TIMED(KC_FDM_BWD, k_fdm_bwd(st, X32, dX1_32, A, mA, vA, nullptr, slot, F, L, ac, out.update,
                                 dX, nullptr, R, s));
-  TIMED(KC_EMB_GRAD, k_emb_grad(st, ctx, dX, C, E, emb_partial, emb_chunk, emb_sub, R, G_("emb"), s));
+  TIMED(KC_EMB_GRAD, k_emb_grad_partial(st, ctx, dX, C, E, emb_partial, emb_chunk, emb_sub, R, s));
   product(PS_WGRAD, 0, R, s);
-  TIMED(KC_COLSUM, k_colsum(st, d_cs, n_cs, cs_blocks, cs_cols, cs_partial, R, s));
-  if (out.update) TIMED(KC_ADAM, k_adam(st, param, grad, m, v, p16, P, ac, s));
+  if (out.update) {
+    TIMED(KC_COLSUM, k_colsum_partial(st, d_cs, n_cs, cs_blocks, cs_cols, cs_partial, R, s));
+    TIMED(KC_ADAM, k_adam(st, param, grad, m, v, p16, P, ac, d_kind, d_part_jobs, s));
+  } else {
+    TIMED(KC_EMB_GRAD, k_emb_grad_reduce(st, emb_partial, emb_chunk, E, G_("emb"), s));
+    TIMED(KC_COLSUM, k_colsum(st, d_cs, n_cs, cs_blocks, cs_cols, cs_partial, R, s));
+  }
   hip_check(hipGetLastError(), "step launch");
 }
 
