@@ -5,6 +5,18 @@
 
 namespace edpc {
 
+// One element's moments and parameter.  In each moment's sum of two products
+// one is rounded and the other is not: the gradient's is exact, or (OLD) the old
+// moment's.  Which one is part of the result (containers depend on it).
+template <bool OLD = false>
+__device__ __forceinline__ void adam1(float& P, float& M, float& V, float g, float lr_bc, float inv_bc2,
+                                      const AdamCfg& ac) {
+  const float dm = 1.0f - ac.beta1, dv = (1.0f - ac.beta2) * g;
+  M = OLD ? fmaf(ac.beta1, M, dm * g) : fmaf(dm, g, ac.beta1 * M);
+  V = OLD ? fmaf(ac.beta2, V, dv * g) : fmaf(g, dv, ac.beta2 * V);
+  P = P - lr_bc * M / (sqrtf(V * inv_bc2) + ac.eps);
+}
+
 // The Adam step (Kingma & Ba 2015, bias-corrected) on 8 parameters P with
 // moments M, V and gradients gv, in place; lr_bc = lr / (1 - beta1^tau),
 // inv_bc2 = 1 / (1 - beta2^tau).
@@ -110,9 +122,9 @@ __device__ __forceinline__ void adam_elements(const StepState* st, const AdamJob
   } else {
     gr = g[o];
   }
-  const float mm = ac.beta1 * m[o] + (1.0f - ac.beta1) * gr;
-  const float vv = ac.beta2 * v[o] + (1.0f - ac.beta2) * gr * gr;
-  p[o] -= lr_bc * mm / (sqrtf(vv * inv_bc2) + ac.eps);
+  float pp = p[o], mm = m[o], vv = v[o];
+  adam1(pp, mm, vv, gr, lr_bc, inv_bc2, ac);
+  p[o] = pp;
   m[o] = mm;
   v[o] = vv;
 }

@@ -129,13 +129,14 @@ hipError_t launch_gemm(int tile, bool bf16, bool a_kmajor, bool b_kmajor, EpiKin
 // one work-group per tile.
 hipError_t launch_wgrad(int tile, bool bf16, const WgradProblem* d_probs, int n_probs,
                         int total_tiles, const StepState* st, float* part, hipStream_t s);
-// The same weight gradients with Adam in the epilogue (4-wave tiles only;
-// M and N multiples of 32, the shared weights of the row-block step), plus
-// elem_items work-groups of element-range Adam (ad.ejobs).  Returns
-// hipErrorInvalidValue for other tiles.
-hipError_t launch_wgrad_adam(int tile, const WgradProblem* d_probs, int n_probs, int total_tiles,
-                             int elem_items, const StepState* st, const WgradAdam& ad,
-                             hipStream_t s);
+// The same weight gradients, BF16, with Adam in the epilogue, on tiles of edge
+// x edge (M and N multiples of 32, the shared weights of the row-block step;
+// tile_begin and tiles_n for that edge), plus elem_items work-groups of
+// element-range Adam (ad.ejobs).  Edge 64 sums by the 32 x 32 x 16 instruction,
+// edge 32 by the 16 x 16 x 32 one, as the tile ids of wgrad_adam_edge do.
+inline int wgrad_adam_edge(int tile) { return tile >= TILE_64x64 ? 64 : 32; }
+hipError_t launch_wgrad_adam(int edge, const WgradProblem* d_probs, int n_probs, int total_tiles,
+                             int elem_items, const StepState* st, const WgradAdam& ad, hipStream_t s);
 // FP32 products (gemm_fp32.hip) and wide tiles (gemm_wide.hip), reached
 // through the launchers above.
 hipError_t launch_gemm_fp32(int tile, bool a_kmajor, bool b_kmajor, EpiKind epi, int nb,

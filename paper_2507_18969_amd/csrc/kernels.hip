@@ -1,4 +1,5 @@
 // Row-wise / element-wise kernels of one model step and the coder lanes.
+#include "adam.h"
 #include "kernels.h"
 #include "head_row.h"
 
@@ -980,7 +981,7 @@ __global__ void __launch_bounds__(256) adam_kernel(const StepState* __restrict__
   const float lr_bc = ac.lr / st->bc1;
   const float inv_bc2 = 1.0f / st->bc2;
   float gr = g[i];
-  const float m0 = m[i], v0 = v[i], p0 = p[i];
+  float m0 = m[i], v0 = v[i], p0 = p[i];
   const int k = __builtin_amdgcn_readfirstlane((int)kind[i >> 6]);
   if (k) {
     const PartialJob jb = jobs[k - 1];
@@ -989,14 +990,11 @@ __global__ void __launch_bounds__(256) adam_kernel(const StepState* __restrict__
     gr = ordered_sum(jb.part + e, (size_t)jb.ld, (st->rows + jb.part_rows - 1) / jb.part_rows);
     g[i] = gr;
   }
-  // which product of a sum is rounded is part of the result: containers depend on it
-  const float mm = fmaf(1.0f - ac.beta1, gr, ac.beta1 * m0);
-  const float vv = fmaf(gr, (1.0f - ac.beta2) * gr, ac.beta2 * v0);
-  const float pp = p0 - lr_bc * mm / (sqrtf(vv * inv_bc2) + ac.eps);
-  m[i] = mm;
-  v[i] = vv;
-  p[i] = pp;
-  if (p16) p16[i] = f2bf(pp);
+  adam1(p0, m0, v0, gr, lr_bc, inv_bc2, ac);
+  m[i] = m0;
+  v[i] = v0;
+  p[i] = p0;
+  if (p16) p16[i] = f2bf(p0);
 }
 
 void k_adam(const StepState* st, float* p, float* g, float* m, float* v, bf16_t* p16, size_t n,

@@ -153,8 +153,7 @@ struct Model {
     WgradProblem* d = nullptr;
     int n = 0, tiles = 0;
     std::vector<WgradProblem> host;
-    WgradProblem* d_adam = nullptr;  // row-block step: the same with fragment copies (Adam launch)
-  } wg_tab[TILE_COUNT];
+  } wg_tab[TILE_COUNT], wg_adam[2];  // wg_adam: row-block step, tiles of edge 32 and 64 with fragment copies
   float* wg_part = nullptr;  // scratch of the balanced wide-tile weight-gradient launch
   size_t wg_part_floats = 0;
   ColsumJob* d_cs = nullptr;

@@ -218,12 +218,9 @@ KernelConfig Model::default_config(const edpc_config& c, size_t rows) {
   k.fused = !(c.flags & EDPC_CFG_LAYERWISE) && c.precision == EDPC_BF16 && rows <= (1u << 20) &&
             !(c.flags & (EDPC_CFG_NO_LTE | EDPC_CFG_LOW_RANK)) &&
             fused_supported(F, L, H, (int)c.branches, (int)c.blocks);
-  // The row-block step's update applies Adam in the epilogue of a 4-wave
-  // weight-gradient tile (a wide tile would need a separate Adam pass).  That
-  // epilogue favours larger tiles over more of them: at 1024 rows of the
-  // 1024-stream model an update step took 248 us on 64 x 128 or 128 x 64
-  // tiles (224 of them) against 284 us on the 64 x 32 ones the general rule
-  // picks for 512 tiles (896); the 192-tile rule above gives 128 x 64.
+  // The row-block step's update applies Adam to each weight-gradient tile (a
+  // wide tile would need a separate Adam pass); the id gives the sums, and the
+  // kernel takes its own tiles for them.
   if (k.fused && k.tile[PS_WGRAD] >= TILE_W128x128) k.tile[PS_WGRAD] = TILE_64x128;
   // from 4096 rows the LayerNorm adjoint forms its block's column sums itself
   // (16 rows a workgroup in turn); below that its workgroups would be too few
@@ -746,8 +743,10 @@ void Model::setup_fused() {
     n_adam_elem_jobs = (int)ae.size();
     adam_elem_items = items;
     tables.add(&d_adam_elem_jobs, ae);
-    for (int tile = 0; tile < TILE_W128x128; ++tile) {
-      std::vector<WgradProblem> wp = wg_tab[tile].host;
+    for (int e = 0; e < 2; ++e) {
+      const int edge = e ? 64 : 32;
+      std::vector<WgradProblem> wp = wg_tab[0].host;
+      int tiles = 0;
       bool ok = !wp.empty();
       for (WgradProblem& p : wp) {
         p.nt = p.nn = nullptr;
@@ -757,9 +756,14 @@ void Model::setup_fused() {
             p.nn = const_cast<uint4*>(fm.nn);
           }
         if (!p.nt || p.M % 32 || p.N % 32) ok = false;
+        p.tiles_n = (p.N + edge - 1) / edge;
+        p.tile_begin = tiles;
+        tiles += p.tiles_n * ((p.M + edge - 1) / edge);
       }
       if (!ok) continue;
-      tables.add(&wg_tab[tile].d_adam, wp);
+      wg_adam[e].n = (int)wp.size();
+      wg_adam[e].tiles = tiles;
+      tables.add(&wg_adam[e].d, wp);
     }
   }
   fout.colpart_cols = cols;
@@ -902,14 +906,14 @@ void Model::step(StepMode mode, const StreamIO& io, const StepOutputs& out, int 
                                 L, L, ac, out.update, dX1_32, dX1_16, R, s));
     TIMED(KC_EMB_GRAD, hip_check(launch_fused_out(F, L, fout, R, s), "fused out launch"));
     const int wt = kc.tile[PS_WGRAD];
-    if (out.update && wt < TILE_W128x128 && wg_tab[wt].d_adam) {
+    const int edge = wgrad_adam_edge(wt);
+    const WgTable& t = wg_adam[edge / 64];
+    if (out.update && wt < TILE_W128x128 && t.d) {
       // each weight tile takes Adam and its fragment rewrite as soon as its
       // gradient is summed; work-groups past the tiles take the biases,
       // LayerNorm and embedding (their partials are complete by now)
-      const WgTable& t = wg_tab[wt];
       const WgradAdam ad{grad, param, m, v, ac, 0, d_adam_elem_jobs, n_adam_elem_jobs};
-      TIMED(PS_WGRAD, hip_check(launch_wgrad_adam(wt, t.d_adam, t.n, t.tiles, adam_elem_items, st,
-                                                  ad, s),
+      TIMED(PS_WGRAD, hip_check(launch_wgrad_adam(edge, t.d, t.n, t.tiles, adam_elem_items, st, ad, s),
                                 "wgrad launch"));
       return;
     }
