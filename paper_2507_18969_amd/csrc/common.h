@@ -127,6 +127,31 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// A 4 x 16 block of 16-bit values in LDS, by 16 lanes: lane i gives the address
+// of values 4 (i mod 4) .. of row i / 4 and gets column i.  Two such blocks (k 0
+// .. 3 and 4 .. 7 of the lane's group) make a BF16 MFMA operand.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ s16x4 lds_read_tr(const char* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
+}
+__device__ __forceinline__ bf16x8 lds_frag_tr(const char* lo, const char* hi) {
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lds_read_tr(lo), lds_read_tr(hi), 0, 1, 2, 3,
+                                                            4, 5, 6, 7));
+}
+
+// Index of the last of n entries with begin <= x (entry 0 begins at 0): one
+// round of loads for 64 entries instead of a chain of dependent ones.
+template <class Job, class Begin>
+__device__ __forceinline__ int find_entry(const Job* jobs, int n, int x, Begin begin) {
+  const int lane = threadIdx.x & 63;
+  int at = -1;
+  for (int b = 0; b < n; b += 64) {
+    const bool le = b + lane < n && begin(jobs[b + lane < n ? b + lane : 0]) <= x;
+    at += __popcll(__ballot(le));
+  }
+  return __builtin_amdgcn_readfirstlane(at);
+}
+
 // p[0] + p[stride] + ... + p[(n-1) stride], added strictly in index order;
 // the loads are issued 32 at a time so their latencies overlap (slots past n
 // add an exact zero).

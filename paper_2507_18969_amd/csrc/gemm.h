@@ -141,8 +141,10 @@ hipError_t launch_wgrad_adam(int edge, const WgradProblem* d_probs, int n_probs,
 // through the launchers above.
 hipError_t launch_gemm_fp32(int tile, bool a_kmajor, bool b_kmajor, EpiKind epi, int nb,
                             const GemmArgs& g, int grid_m_max, hipStream_t s);
+// sums: what else to sum in the launch (kernels.h), over at most max_rows rows, or null
+struct GradSums;
 hipError_t launch_wgrad_fp32(int tile, const WgradProblem* d_probs, int n_probs, int total_tiles,
-                             const StepState* st, hipStream_t s);
+                             const StepState* st, const GradSums* sums, int max_rows, hipStream_t s);
 hipError_t launch_gemm_wide(int tile, bool a_kmajor, bool b_kmajor, EpiKind epi, int nb,
                             const GemmArgs& g, int grid_m_max, hipStream_t s);
 hipError_t launch_wgrad_wide(int tile, const WgradProblem* d_probs, int n_probs, int total_tiles,

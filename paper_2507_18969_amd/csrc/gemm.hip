@@ -423,7 +423,7 @@ hipError_t launch_wgrad(int tile, bool bf16, const WgradProblem* d_probs, int n_
     return launch_wgrad_wide(tile, d_probs, n_probs, total_tiles, st, part, s);
   }
   return bf16 ? launch_wp(tile, d_probs, n_probs, total_tiles, st, s)
-              : launch_wgrad_fp32(tile, d_probs, n_probs, total_tiles, st, s);
+              : launch_wgrad_fp32(tile, d_probs, n_probs, total_tiles, st, nullptr, 0, s);
 }
 
 }  // namespace edpc

@@ -158,6 +158,17 @@ void k_emb_grad_reduce(const StepState* st, const float* partial, int chunk_rows
 void emb_grad_plan(int max_rows, int C, int E, int* chunk_rows, int* sub_rows);
 void k_emb_grad_partial(const StepState* st, const uint8_t* ctx, const float* dx, int C, int E,
                         float* partial, int chunk_rows, int sub_rows, int max_rows, hipStream_t s);
+// What the launch of the FP32 weight gradients sums beside them: the first pass
+// of the column sums and the embedding gradient's partials.
+struct GradSums {
+  const ColsumJob* jobs;
+  int n_jobs, col_blocks, total_cols;
+  float* col_partial;
+  const uint8_t* ctx;
+  const float* dx;
+  int C, E, chunk_rows, sub_rows;
+  float* emb_partial;
+};
 // Gradient of `cols` elements at offset off of the flat buffers: the in-order
 // sum of part[k * ld + e] over the ceil(rows / part_rows) partials.
 struct PartialJob {

@@ -1,6 +1,6 @@
 // Row-wise / element-wise kernels of one model step and the coder lanes.
 #include "adam.h"
-#include "kernels.h"
+#include "grad_sums.h"
 #include "head_row.h"
 
 #include <algorithm>
@@ -671,47 +671,14 @@ void k_head(const StepState* st, HeadArgs a, StreamIO io, int max_rows, hipStrea
 }
 
 // ---------------------------------------------------------------------------
-// Column sums over the active rows (bias and LayerNorm affine gradients).
-// Two passes with a fixed order: rows are cut into chunks of kColChunk; a
-// block sums 64 columns of one chunk (4 interleaved row slices added in slice
-// order) into partial[chunk][col]; the second pass adds the chunks in order.
+// Column sums and embedding gradient by themselves (grad_sums.h)
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) colsum_partial_kernel(const StepState* __restrict__ st,
                                                              const ColsumJob* __restrict__ jobs,
                                                              int n_jobs, int total_cols,
                                                              float* __restrict__ partial) {
-  const int rows = st->rows;
-  const int r0 = blockIdx.y * kColChunk;
-  if (r0 >= rows) return;
-  int j = 0;
-  while (j + 1 < n_jobs && (int)blockIdx.x >= jobs[j + 1].col_block_begin) ++j;
-  const ColsumJob jb = jobs[j];
-  const int lc = ((int)blockIdx.x - jb.col_block_begin) * 64 + (threadIdx.x & 63);
-  const int slice = threadIdx.x >> 6;
-  const int r1 = min(rows, r0 + kColChunk);
-  float acc = 0.f;
-  const auto src = gl(jb.src);
-  if (lc < jb.cols) {
-    if (jb.h) {
-      const auto h = gl(jb.h), mean = gl(jb.mean), rstd = gl(jb.rstd);
-#pragma unroll 4
-      for (int r = r0 + slice; r < r1; r += 4) {
-        const float xh = (h[(size_t)r * jb.ld + lc] - mean[r]) * rstd[r];
-        acc += src[(size_t)r * jb.ld + lc] * xh;
-      }
-    } else {
-#pragma unroll 4
-      for (int r = r0 + slice; r < r1; r += 4) acc += src[(size_t)r * jb.ld + lc];
-    }
-  }
-  __shared__ float part[4][64];
-  part[slice][threadIdx.x & 63] = acc;
-  __syncthreads();
-  if (slice == 0 && lc < jb.cols) {
-    const int t = threadIdx.x;
-    partial[(size_t)blockIdx.y * total_cols + jb.col_offset + lc] =
-        (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]);
-  }
+  __shared__ float part[256];
+  colsum_block(st, jobs, n_jobs, total_cols, partial, blockIdx.x, blockIdx.y, part);
 }
 
 __global__ void colsum_reduce_kernel(const StepState* __restrict__ st,
@@ -760,161 +727,14 @@ void k_colsum_reduce(const StepState* st, const ColsumJob* jobs, int n_jobs, int
                      jobs, n_jobs, total_cols, partial, chunk_rows);
 }
 
-// ---------------------------------------------------------------------------
-// Embedding gradient: dEmb[v] = sum over (row, position) with ctx = v of the
-// matching E-slice of dX.  A block takes a chunk of rows, staged through LDS
-// a few rows at a time; thread v keeps the E sums of byte value v in
-// registers and adds the matching pairs in row-major pair order.  The chunk
-// partials are then added in chunk order.
-// ---------------------------------------------------------------------------
 template <int E>
-__global__ void __launch_bounds__(256) emb_grad_partial_kernel(
-    const StepState* __restrict__ st, const uint8_t* __restrict__ ctx, const float* __restrict__ dx,
-    int C, int chunk_rows, int sub_rows, float* __restrict__ partial) {
-  // dEmb_chunk[v][e] = sum over the chunk's (row, position) pairs of
-  // [ctx = v] * dX[row][position*E + e]: a matrix product on the BF16 MFMA
-  // whose A operand, the one-hot of the context bytes, is formed in registers
-  // (exact in BF16).  An FP32 value x is the exact sum of three BF16 values
-  // (x rounded to 8 significant bits, then the rounding errors of what is
-  // left), so dX enters as three BF16 operands accumulated in FP32: an FP32
-  // sum of the same terms, 3 MFMA instructions per 32 pairs where the FP32
-  // MFMA (K = 4) takes 8.
-  // Wave w owns byte values 64w .. 64w+63; pairs are visited in row-major
-  // order, 32 per step.
-  extern __shared__ float smem_f[];
-  float* lds_dx = smem_f;                                            // [sub_rows][F]
-  uint8_t* lds_ctx = (uint8_t*)(smem_f + (size_t)sub_rows * C * E);  // [sub_rows][C]
-  constexpr int NE = E / 16;
-  const int rows = st->rows;
-  const int F = C * E;
-  const int r0 = blockIdx.x * chunk_rows;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  f32x4 acc[4][NE];
-#pragma unroll
-  for (int vb = 0; vb < 4; ++vb)
-#pragma unroll
-    for (int nb = 0; nb < NE; ++nb) acc[vb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int r_end = min(rows, r0 + chunk_rows);
-  // The next sub-batch of rows is loaded into registers while the current
-  // one feeds the MFMAs from LDS: up to 8192 floats of dX (8 float4 a
-  // thread) and 512 context bytes (sub_rows * C <= 8192 / E).  Wider rows
-  // (F > 8192, one row a sub-batch) are copied straight to LDS instead.
-  constexpr int kStage = 8;
-  const bool staged = sub_rows * F <= 4 * kStage * 256;
-  float4 nx[kStage];
-  uint32_t nc[2] = {0u, 0u};
-  auto fetch = [&](int rs) {
-    const int nr = min(sub_rows, r_end - rs);
-    const float4* src = (const float4*)(dx + (size_t)rs * F);
-#pragma unroll
-    for (int q = 0; q < kStage; ++q) {
-      const int k = (int)threadIdx.x + 256 * q;
-      nx[q] = k < nr * F / 4 ? src[k] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int k = (int)threadIdx.x + 256 * q;
-      nc[q] = k < nr * C ? (uint32_t)ctx[(size_t)rs * C + k] : 0u;
-    }
-  };
-  if (staged && r0 < r_end) fetch(r0);
-  for (int rs = r0; rs < r_end; rs += sub_rows) {
-    const int nr = min(sub_rows, r_end - rs);
-    __syncthreads();  // the previous sub-batch's LDS reads are done
-    if (staged) {
-#pragma unroll
-      for (int q = 0; q < kStage; ++q) {
-        const int k = (int)threadIdx.x + 256 * q;
-        if (k < nr * F / 4) ((float4*)lds_dx)[k] = nx[q];
-      }
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int k = (int)threadIdx.x + 256 * q;
-        if (k < nr * C) lds_ctx[k] = (uint8_t)nc[q];
-      }
-    } else {
-      const float4* src = (const float4*)(dx + (size_t)rs * F);
-      for (int k = threadIdx.x; k < nr * F / 4; k += 256) ((float4*)lds_dx)[k] = src[k];
-      for (int k = threadIdx.x; k < nr * C; k += 256) lds_ctx[k] = ctx[(size_t)rs * C + k];
-    }
-    __syncthreads();
-    if (staged && rs + sub_rows < r_end) fetch(rs + sub_rows);
-    // lane group g = lane / 16 takes pairs p0 .. p0 + 7 of each 32-pair step;
-    // pairs past the chunk's end take no byte value and a zero dX
-    const int np = nr * C;
-    for (int k0 = 0; k0 < np; k0 += 32) {
-      const int p0 = k0 + 8 * (lane >> 4);
-      int off[8];  // LDS offset of each pair's dX, or -1
-      uint32_t bytes[8];
-      if (C % 8 == 0) {  // the 8 pairs lie in one row: all valid or none
-        const bool live = p0 < np;
-        const int pr = live ? p0 / C : 0, pc = live ? p0 - pr * C : 0;
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          off[v] = live ? pr * F + (pc + v) * E : -1;
-          bytes[v] = live ? (uint32_t)lds_ctx[p0 + v] : 0xFFFFu;
-        }
-      } else {
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          const int p = p0 + v;
-          const int pr = p / C;
-          off[v] = p < np ? pr * F + (p - pr * C) * E : -1;
-          bytes[v] = p < np ? (uint32_t)lds_ctx[p] : 0xFFFFu;
-        }
-      }
-#pragma unroll
-      for (int nb = 0; nb < NE; ++nb) {
-        const float* d = lds_dx + 16 * nb + (lane & 15);
-        uint32_t hi[4], mid[4], lo[4];
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-          uint32_t ph = 0, pm = 0, pl = 0;
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            const int o = off[2 * h + u];
-            const float x = o >= 0 ? d[o] : 0.0f;
-            const bf16_t b0 = f2bf(x);
-            const float r1 = x - bf2f(b0);
-            const bf16_t b1 = f2bf(r1);
-            const bf16_t b2 = f2bf(r1 - bf2f(b1));
-            ph |= (uint32_t)b0 << (16 * u);
-            pm |= (uint32_t)b1 << (16 * u);
-            pl |= (uint32_t)b2 << (16 * u);
-          }
-          hi[h] = ph;
-          mid[h] = pm;
-          lo[h] = pl;
-        }
-        const bf16x8 bh = __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
-        const bf16x8 bm = __builtin_bit_cast(bf16x8, make_uint4(mid[0], mid[1], mid[2], mid[3]));
-        const bf16x8 bl = __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
-#pragma unroll
-        for (int vb = 0; vb < 4; ++vb) {
-          const uint32_t me = (uint32_t)(64 * w + 16 * vb + (lane & 15));
-          uint32_t q[4];
-#pragma unroll
-          for (int h = 0; h < 4; ++h)
-            q[h] = (bytes[2 * h] == me ? 0x3F80u : 0u) |
-                   ((bytes[2 * h + 1] == me ? 0x3F80u : 0u) << 16);
-          const bf16x8 a = __builtin_bit_cast(bf16x8, make_uint4(q[0], q[1], q[2], q[3]));
-          acc[vb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bh, acc[vb][nb], 0, 0, 0);
-          acc[vb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bm, acc[vb][nb], 0, 0, 0);
-          acc[vb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bl, acc[vb][nb], 0, 0, 0);
-        }
-      }
-    }
-  }
-  float* out = partial + (size_t)blockIdx.x * 256 * E;
-#pragma unroll
-  for (int vb = 0; vb < 4; ++vb)
-#pragma unroll
-    for (int nb = 0; nb < NE; ++nb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int v = 64 * w + 16 * vb + 4 * (lane >> 4) + r;
-        out[(size_t)v * E + 16 * nb + (lane & 15)] = acc[vb][nb][r];
-      }
+__global__ void __launch_bounds__(256) emb_grad_partial_kernel(const StepState* __restrict__ st,
+                                                               const uint8_t* __restrict__ ctx,
+                                                               const float* __restrict__ dx, int C,
+                                                               int chunk_rows, int sub_rows,
+                                                               float* __restrict__ partial) {
+  extern __shared__ __align__(16) char smem[];
+  emb_grad_block<E>(st->rows, ctx, dx, C, chunk_rows, sub_rows, partial, blockIdx.x, smem);
 }
 
 __global__ void emb_grad_reduce_kernel(const StepState* __restrict__ st,
@@ -946,7 +766,7 @@ void k_emb_grad_reduce(const StepState* st, const float* partial, int chunk_rows
 void k_emb_grad_partial(const StepState* st, const uint8_t* ctx, const float* dx, int C, int E,
                         float* partial, int chunk_rows, int sub_rows, int max_rows, hipStream_t s) {
   const int nb = (max_rows + chunk_rows - 1) / chunk_rows;
-  const size_t smem = (size_t)sub_rows * C * E * sizeof(float) + (size_t)sub_rows * C + 32;
+  const size_t smem = emb_lds_bytes(sub_rows, C, E);
 #define EMB_CASE(EE)                                                                            \
   case EE:                                                                                      \
     if (smem > 65536)  /* the widest feature vectors need more than the default LDS */          \

@@ -978,14 +978,21 @@ void Model::step(StepMode mode, const StreamIO& io, const StepOutputs& out, int 
   if (low_rank)
     TIMED(KC_FDM_BWD, k_fdm_bwd(st, X32, dX1_32, A, mA, vA, nullptr, slot, F, L, ac, out.update,
                                 dX, nullptr, R, s));
-  TIMED(KC_EMB_GRAD, k_emb_grad_partial(st, ctx, dX, C, E, emb_partial, emb_chunk, emb_sub, R, s));
-  product(PS_WGRAD, 0, R, s);
-  if (out.update) {
+  if (bf16) {
+    TIMED(KC_EMB_GRAD, k_emb_grad_partial(st, ctx, dX, C, E, emb_partial, emb_chunk, emb_sub, R, s));
+    product(PS_WGRAD, 0, R, s);
     TIMED(KC_COLSUM, k_colsum_partial(st, d_cs, n_cs, cs_blocks, cs_cols, cs_partial, R, s));
+  } else {
+    const GradSums gs{d_cs, n_cs, cs_blocks, cs_cols, cs_partial, ctx, dX, C, E, emb_chunk, emb_sub, emb_partial};
+    const WgTable& t = wg_tab[kc.tile[PS_WGRAD]];
+    TIMED(PS_WGRAD, hip_check(launch_wgrad_fp32(kc.tile[PS_WGRAD], t.d, t.n, t.tiles, st, &gs, R, s),
+                              "wgrad launch"));
+  }
+  if (out.update) {
     TIMED(KC_ADAM, k_adam(st, param, grad, m, v, p16, P, ac, d_kind, d_part_jobs, s));
   } else {
     TIMED(KC_EMB_GRAD, k_emb_grad_reduce(st, emb_partial, emb_chunk, E, G_("emb"), s));
-    TIMED(KC_COLSUM, k_colsum(st, d_cs, n_cs, cs_blocks, cs_cols, cs_partial, R, s));
+    TIMED(KC_COLSUM, k_colsum_reduce(st, d_cs, n_cs, cs_cols, cs_partial, kColChunk, s));
   }
   hip_check(hipGetLastError(), "step launch");
 }

@@ -64,26 +64,6 @@ struct WaMma<16> {
   __device__ static int row(int r, int lane) { return 4 * (lane >> 4) + r; }
 };
 
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ s16x4 lds_read_tr(const char* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) s16x4*)p);
-}
-
-// Index of the last of n entries with begin <= x (entry 0 begins at 0): one
-// round of loads for 64 entries instead of a chain of dependent ones.
-template <class Job, class Begin>
-__device__ __forceinline__ int find_entry(const Job* jobs, int n, int x, Begin begin) {
-  const int lane = threadIdx.x & 63;
-  int at = -1;
-  for (int b = 0; b < n; b += 64) {
-    const bool le = b + lane < n && begin(jobs[b + lane < n ? b + lane : 0]) <= x;
-    at += __popcll(__ballot(le));
-  }
-  return __builtin_amdgcn_readfirstlane(at);
-}
-
 template <int MB>
 __global__ void __launch_bounds__(256) wgrad_adam_kernel(const WgradProblem* __restrict__ probs, int n_probs,
                                                          const StepState* __restrict__ st, WgradAdam ad) {
@@ -137,10 +117,7 @@ __global__ void __launch_bounds__(256) wgrad_adam_kernel(const WgradProblem* __r
   const int lk = 8 * (lane / MB) + ((lane & 15) >> 2), lc = (lane & 16 & (MB - 1)) + 4 * (lane & 3);
   const int fa0 = lk * W::ROW + 2 * (wm * MB + lc);
   const int fb0 = W::OPER + lk * W::ROW + 2 * (wn * MB + lc);
-  auto frag = [&](const char* p) {
-    const s16x4 lo = lds_read_tr(p), hi = lds_read_tr(p + 4 * W::ROW);
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-  };
+  auto frag = [&](const char* p) { return lds_frag_tr(p, p + 4 * W::ROW); };
   constexpr int KS = W::BK / Op::K;
   typename Op::Acc acc;
 #pragma unroll
