@@ -24,7 +24,7 @@ CSRC = os.path.join(PKG, "csrc")
 ROOT = os.path.dirname(PKG)
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libedpc.so")
-SOURCES = ["gemm.hip", "gemm_fp32.hip", "gemm_wide.hip", "wgrad_adam.hip", "kernels.hip", "fused.hip", "model.hip", "codec.hip", "stream.hip", "ksg.hip", "memory.hip", "api.hip"]
+SOURCES = ["gemm.hip", "gemm_fp32.hip", "gemm_wide.hip", "wgrad_adam.hip", "fused_fp32.hip", "kernels.hip", "fused.hip", "model.hip", "codec.hip", "stream.hip", "ksg.hip", "memory.hip", "api.hip"]
 
 HIPCC = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")

@@ -6,6 +6,7 @@
 
 #include "../../include/edpc.h"
 #include "fused.h"
+#include "fused_fp32.h"
 #include "gemm.h"
 #include "kernels.h"
 #include "memory.h"
@@ -159,6 +160,7 @@ struct Model {
   ColsumJob* d_cs = nullptr;
   int n_cs = 0, cs_blocks = 0, cs_cols = 0;
   float* cs_partial = nullptr;
+  FusedFp32Args f32a{};  // FP32 row-block kernel (st null: not taken)
   PartialJob* d_part_jobs = nullptr;  // layer-by-layer Adam: sums formed on the way, and which
   uint8_t* d_kind = nullptr;          // elements take them
   std::vector<float*> ln_part;  // LayerNorm adjoint's row-group column sums, per block (or empty)
@@ -213,6 +215,7 @@ struct Model {
   // bounds the launch grids (>= st->rows).
   // sched: when given (coding steps), the first kernel sets the step state and
   // gathers the contexts itself; without it both are taken as already set.
+  bool row_block_fp32(int grid_rows) const;
   void step(StepMode mode, const StreamIO& io, const StepOutputs& out, int grid_rows,
             hipStream_t s, const StepSched* sched = nullptr);
 

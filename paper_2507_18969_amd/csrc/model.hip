@@ -535,6 +535,49 @@ void Model::build_tables(hipStream_t s) {
   lj.col_offset = 0;
   lj.scale = 0.0f;  // scale by 1/rows
   loss_partial = mem.take<float>(colsum_partial_elems((int)max_rows, 1));
+  // FP32 row-block step: a shape of the kernel, sums of its own for the LayerNorm's
+  // columns not asked for, blocks whose arrays lie at equal distances
+  f32a = FusedFp32Args{};
+  if (!bf16 && lte && !low_rank && ln_part.empty() && !(cfg.flags & EDPC_CFG_LAYERWISE) &&
+      fused_fp32_supported(F, L, H, K)) {
+    bool even = true;
+    auto arr = [&](auto& out, auto at) {
+      if (N == 0) return;
+      out.p = at(0);
+      out.stride = N > 1 ? at(1) - at(0) : 0;
+      for (int j = 2; j < N; ++j) even = even && at(j) - at(0) == j * out.stride;
+    };
+    auto par = [&](const char* a, const char* b) {
+      return [=](int j) { return (const float*)P_(a + std::to_string(j) + b); };
+    };
+    arr(f32a.gamma, par("ln", ".gamma"));
+    arr(f32a.beta, par("ln", ".beta"));
+    arr(f32a.w0, par("blk", ".w0"));
+    arr(f32a.b0, par("blk", ".b0"));
+    arr(f32a.wo, par("blk", ".wo"));
+    arr(f32a.bo, par("blk", ".bo"));
+    arr(f32a.h, [&](int j) { return Hs[j]; });
+    arr(f32a.z, [&](int j) { return Z32[j]; });
+    arr(f32a.mean, [&](int j) { return mean[j]; });
+    arr(f32a.rstd, [&](int j) { return rstd[j]; });
+    arr(f32a.abr, [&](int j) { return Abr[j]; });
+    arr(f32a.g, [&](int j) { return G32[j]; });
+    arr(f32a.da, [&](int j) { return dA32[j]; });
+    arr(f32a.dz, [&](int j) { return dZ[j]; });
+    arr(f32a.dh, [&](int j) { return dH32[j]; });
+    f32a.n_blocks = N;
+    f32a.L = L;
+    f32a.H = H;
+    f32a.y = Y32;
+    f32a.w2 = P_("w2");
+    f32a.b2 = P_("b2");
+    f32a.wh = P_("wh");
+    f32a.bh = P_("bh");
+    f32a.hn = Hs[N];
+    f32a.dhn = dH32[N];
+    f32a.dy = dY;
+    if (even) f32a.st = st;
+  }
   tables.add(&d_loss_job, &lj, 1);
   if (kc.fused) setup_fused();
   tables.commit(mem, s);
@@ -782,6 +825,16 @@ static GemmArgs ga() {
   return g;
 }
 
+// Whether an FP32 step on a grid of R rows takes the row-block kernel: the model
+// allows it (f32a), its sums are those of the products' tiles (the 16 x 16 x 4
+// instruction), and R is in its range.
+bool Model::row_block_fp32(int R) const {
+  if (!f32a.st || R > kFusedFp32Rows) return false;
+  for (int ps : {PS_LTE_UP, PS_GATE, PS_OUT, PS_HEAD, PS_HEAD_BWD, PS_GATE_BWD, PS_DZ, PS_LTE_UP_BWD})
+    if (kc.tile[ps] > TILE_32x64) return false;
+  return true;
+}
+
 // One dense product of the step; j = block index where it applies.
 void Model::product(int ps, int j, int R, hipStream_t s) {
   const std::string b = "blk" + std::to_string(j);
@@ -937,35 +990,44 @@ void Model::step(StepMode mode, const StreamIO& io, const StepOutputs& out, int 
   if (lte) product(PS_LTE_DOWN, 0, R, s);
   if (low_rank) TIMED(KC_FDM_FWD, k_fdm_fwd(st, X32, A, slot, F, L, X1, nullptr, R, s));  // x' = x A_s
   TIMED(KC_FDM_FWD, k_fdm_fwd(st, X1, U, slot, L, L, Y32, Y16, R, s));  // Eq. 15
-  if (lte) product(PS_LTE_UP, 0, R, s);
-  if (low_rank) TIMED(KC_FDM_FWD, k_fdm_fwd(st, Y32, B, slot, L, F, Hs[0], nullptr, R, s));  // x'' = y B_s
-  for (int j = 0; j < N; ++j) {
-    const std::string ln = "ln" + std::to_string(j);
-    TIMED(KC_LN_FWD, k_ln_fwd(st, Hs[j], P_(ln + ".gamma"), P_(ln + ".beta"), F,
-                              bf16 ? nullptr : Z32[j], bf16 ? Z16[j] : nullptr, mean[j],
-                              rstd[j], R, s));
-    product(PS_GATE, j, R, s);
-    product(PS_OUT, j, R, s);
+  const bool row_block = row_block_fp32(R);
+  if (row_block) {  // Eq. 16 .. head .. coder .. adjoint back to dY, one workgroup per 16 rows
+    FusedFp32Args a = f32a;
+    a.head = ha;
+    TIMED(KC_FUSED, hip_check(launch_fused_fp32(a, K, hio, R, s), "fused launch"));
+  } else {
+    if (lte) product(PS_LTE_UP, 0, R, s);
+    if (low_rank) TIMED(KC_FDM_FWD, k_fdm_fwd(st, Y32, B, slot, L, F, Hs[0], nullptr, R, s));  // x'' = y B_s
+    for (int j = 0; j < N; ++j) {
+      const std::string ln = "ln" + std::to_string(j);
+      TIMED(KC_LN_FWD, k_ln_fwd(st, Hs[j], P_(ln + ".gamma"), P_(ln + ".beta"), F,
+                                bf16 ? nullptr : Z32[j], bf16 ? Z16[j] : nullptr, mean[j],
+                                rstd[j], R, s));
+      product(PS_GATE, j, R, s);
+      product(PS_OUT, j, R, s);
+    }
+    product(PS_HEAD, 0, R, s);
+    TIMED(KC_HEAD, k_head(st, ha, hio, R, s));
   }
-  product(PS_HEAD, 0, R, s);
-  TIMED(KC_HEAD, k_head(st, ha, hio, R, s));
   if (out.loss) {
     TIMED(KC_COLSUM, k_colsum(st, d_loss_job, 1, 1, 1, loss_partial, R, s));
     hip_check(hipMemcpyAsync(out.loss, loss_out, sizeof(float), hipMemcpyDeviceToDevice, s), "copy");
   }
   if (!backward) return;
 
-  // ---- adjoint of the mean cross entropy (Eq. 2) -------------------------
-  product(PS_HEAD_BWD, 0, R, s);
-  for (int j = N - 1; j >= 0; --j) {
-    const std::string ln = "ln" + std::to_string(j);
-    product(PS_GATE_BWD, j, R, s);
-    product(PS_DZ, j, R, s);
-    TIMED(KC_LN_BWD, k_ln_bwd(st, Hs[j], mean[j], rstd[j], P_(ln + ".gamma"), dZ[j],
-                              dH32[j + 1], F, dH32[j], bf16 ? dH16[j] : nullptr,
-                              ln_part.empty() ? nullptr : ln_part[j], R, s));
+  if (!row_block) {
+    // ---- adjoint of the mean cross entropy (Eq. 2) -------------------------
+    product(PS_HEAD_BWD, 0, R, s);
+    for (int j = N - 1; j >= 0; --j) {
+      const std::string ln = "ln" + std::to_string(j);
+      product(PS_GATE_BWD, j, R, s);
+      product(PS_DZ, j, R, s);
+      TIMED(KC_LN_BWD, k_ln_bwd(st, Hs[j], mean[j], rstd[j], P_(ln + ".gamma"), dZ[j],
+                                dH32[j + 1], F, dH32[j], bf16 ? dH16[j] : nullptr,
+                                ln_part.empty() ? nullptr : ln_part[j], R, s));
+    }
+    if (lte) product(PS_LTE_UP_BWD, 0, R, s);
   }
-  if (lte) product(PS_LTE_UP_BWD, 0, R, s);
   // low rank: dy = B_s dx'', dB_s = y (x) dx'' (B before its update), Adam on B_s
   if (low_rank)
     TIMED(KC_FDM_BWD, k_fdm_bwd(st, Y32, dH32[0], B, mB, vB, nullptr, slot, L, F, ac, out.update,
