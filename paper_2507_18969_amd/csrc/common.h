@@ -54,29 +54,75 @@ __device__ __forceinline__ float gelu_grad_f(float x) {
   return cdf + x * pdf;
 }
 
-// Fixed-order wave reductions (butterfly over the 64 lanes).
+// Fixed-order wave reductions: a butterfly over the 64 lanes at distances 32, 16,
+// .. 1, all lanes active.  By lane swaps and DPP: a step is one or two instructions
+// where a shuffle is a round trip through LDS (the BF16 row-block kernel, 1024 rows:
+// 113.8 us with shuffles, 107.4 so).
+// Distances 8 and 4 are rotations in a row of 16, whose values repeat by then.
+template <int CTRL, class T>
+__device__ __forceinline__ T dpp(T v) {
+  return __builtin_bit_cast(
+      T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+template <class T, class Op>
+__device__ __forceinline__ T wave_reduce(T v, Op op) {
+  static_assert(sizeof(T) == 4, "one register");
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  const uint32_t x = __builtin_bit_cast(uint32_t, v);
+  const u32x2 h = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(x, x, false, false));
+  const uint32_t h0 = h[0], h1 = h[1];  // (a bit cast of a vector's element takes its first)
+  v = op(__builtin_bit_cast(T, h0), __builtin_bit_cast(T, h1));
+  const uint32_t y = __builtin_bit_cast(uint32_t, v);
+  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(y, y, false, false));
+  const uint32_t r0 = r[0], r1 = r[1];
+  v = op(__builtin_bit_cast(T, r0), __builtin_bit_cast(T, r1));
+  v = op(v, dpp<0x128>(v));  // row_ror:8
+  v = op(v, dpp<0x124>(v));  // row_ror:4
+  v = op(v, dpp<0x4E>(v));   // quad_perm: 2 3 0 1
+  return op(v, dpp<0xB1>(v));  // 1 0 3 2
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return wave_reduce(v, [](float a, float b) { return a + b; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 __device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return wave_reduce(v, [](int a, int b) { return a + b; });
 }
 __device__ __forceinline__ uint32_t wave_max_u(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    uint32_t w = __shfl_xor(v, o, 64);
-    v = w > v ? w : v;
-  }
+  return wave_reduce(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+}
+// Over each row of 16 lanes, at distances 8, 4, 2, 1.
+__device__ __forceinline__ float row_sum(float v) {
+  v += dpp<0x128>(v);
+  v += dpp<0x124>(v);
+  v += dpp<0x4E>(v);
+  return v + dpp<0xB1>(v);
+}
+// Over the 4 lanes at distances 16 and 32, in this order.
+__device__ __forceinline__ float rows_sum(float v) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  const uint32_t x = __float_as_uint(v);
+  const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(x, x, false, false));
+  const uint32_t y = __float_as_uint(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+  const u32x2 h = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(y, y, false, false));
+  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
+// Sum over lanes 0 .. l, in lane l.
+__device__ __forceinline__ int wave_scan_i(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);   // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);   // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);   // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15, rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31, rows 2 and 3
   return v;
+}
+// Lane `lane`'s value (the same lane in the whole wave), in every lane.
+__device__ __forceinline__ int wave_pick(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+__device__ __forceinline__ float wave_pick(float v, int lane) {
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane));
 }
 
 // Global-memory view of a generic pointer.  Pointers read from device memory

@@ -739,10 +739,8 @@ __global__ void __launch_bounds__(kFusedThreads, 1) fused_kernel(FusedArgs a) {
           czx += dz * x;
         }
         // LayerNorm affine gradients: column sums over the 16 rows
-        cz += __shfl_xor(cz, 16, 64);
-        cz += __shfl_xor(cz, 32, 64);
-        czx += __shfl_xor(czx, 16, 64);
-        czx += __shfl_xor(czx, 32, 64);
+        cz = rows_sum(cz);
+        czx = rows_sum(czx);
         if (lane < 16) {
           sGB[0][c] = cz;
           sGB[1][c] = czx;
@@ -750,11 +748,8 @@ __global__ void __launch_bounds__(kFusedThreads, 1) fused_kernel(FusedArgs a) {
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-#pragma unroll
-        for (int o = 8; o >= 1; o >>= 1) {
-          s1[r] += __shfl_xor(s1[r], o, 64);
-          s2[r] += __shfl_xor(s2[r], o, 64);
-        }
+        s1[r] = row_sum(s1[r]);
+        s2[r] = row_sum(s2[r]);
         if (lc == 0) {
           sRed[w][li + r][0] = s1[r];
           sRed[w][li + r][1] = s2[r];

@@ -46,12 +46,7 @@ __device__ __forceinline__ void row_cdf(int lane, const float z[4], RowCdf& c) {
 
   // exclusive prefix sums
   const int ls = (c.q[0] + c.q[1]) + (c.q[2] + c.q[3]);
-  int incl = ls;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += t;
-  }
+  const int incl = wave_scan_i(ls);
   c.cum[0] = incl - ls;
   c.cum[1] = c.cum[0] + c.q[0];
   c.cum[2] = c.cum[1] + c.q[1];
@@ -75,9 +70,10 @@ __device__ __forceinline__ void row_pick(const RowCdf& c, const float z[4], int 
   const int c0 = c.cum[0], c1 = c.cum[1], c2 = c.cum[2], c3 = c.cum[3];
   const int q0 = c.q[0], q1 = c.q[1], q2 = c.q[2], q3 = c.q[3];
   const float z0 = z[0], z1 = z[1], z2 = z[2], z3 = z[3];
-  *cx = __shfl(jx == 0 ? c0 : jx == 1 ? c1 : jx == 2 ? c2 : c3, x >> 2, 64);
-  *qx = __shfl(jx == 0 ? q0 : jx == 1 ? q1 : jx == 2 ? q2 : q3, x >> 2, 64);
-  *zx = __shfl(jx == 0 ? z0 : jx == 1 ? z1 : jx == 2 ? z2 : z3, x >> 2, 64);
+  const int lx = __builtin_amdgcn_readfirstlane(x >> 2);  // x is the wave's
+  *cx = wave_pick(jx == 0 ? c0 : jx == 1 ? c1 : jx == 2 ? c2 : c3, lx);
+  *qx = wave_pick(jx == 0 ? q0 : jx == 1 ? q1 : jx == 2 ? q2 : q3, lx);
+  *zx = wave_pick(jx == 0 ? z0 : jx == 1 ? z1 : jx == 2 ? z2 : z3, lx);
 }
 
 // Optional per-row outputs: probabilities and the CDF with its closing 2^16.
@@ -108,8 +104,12 @@ __device__ __forceinline__ bool head_row(const StepState* __restrict__ st, const
       d = io.dec[s].d;
       rng = io.dec[s].range;
     }
-    d = __shfl(d, 0, 64);
-    rng = __shfl(rng, 0, 64);
+    auto first = [](uint64_t v) {
+      return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)v) |
+             ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32);
+    };
+    d = first(d);
+    rng = first(rng);
     x = row_decode_symbol(c, d, rng);
   } else if (a.target) {
     x = a.target[r];

@@ -187,9 +187,7 @@ __global__ void __launch_bounds__(256) ksg_select_kernel(const float* __restrict
   // lane where several hold it
   float eps = 0.0f;
   for (int r = 0; r < v; ++r) {
-    float m = best[0];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fminf(m, __shfl_xor(m, o, 64));
+    const float m = wave_reduce(best[0], [](float a, float b) { return fminf(a, b); });
     eps = m;
     const uint64_t holds = __ballot(best[0] == m);
     if (lane == __builtin_ctzll(holds | (1ull << 63))) {
