@@ -76,6 +76,7 @@ struct FusedArgs {
   // head / coder
   HeadArgs head;
   StreamIO io;
+  int row_blocks;  // set by the launcher: workgroups past these read weights ahead
 };
 
 // Row-block kernel before the FDM: context gather (streams) or staged

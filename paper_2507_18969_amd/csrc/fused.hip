@@ -309,9 +309,49 @@ __device__ __forceinline__ void col_sums(const float* lds, int ld_l, int nr, flo
   }
 }
 
+// Workgroup h of an XCD's kAheadPerXcd past the row blocks: a row block's time is
+// that of its weights coming through one CU's misses, and its XCD's L2 (4 MiB) is
+// written anew by every update, so CUs that are idle read the weights into it first,
+// the adjoint's when the forward pass is about halfway (7.3 MB of both do not fit at
+// once).  They only read, and sleep a fixed number of clocks: one s_sleep(127) a
+// quarter MiB, about the rate of a row block.  F 512, 4 blocks, whole updates, without
+// and with: 8 rows 152 and 140 us, 300 rows 174 and 163, 1024 rows 231 and 227, 3000
+// rows 429 and 406 (F 256, all of whose weights fit: 56.2 and 54.7 at 8 rows).
+constexpr int kAheadPerXcd = 8;
+constexpr int kAheadMaxBlocks = 192;  // row blocks that leave as many CUs idle
+template <int F, int L, int H>
+__device__ __forceinline__ void read_weights_ahead(const FusedArgs& a, int h) {
+  auto touch = [&](const uint4* b, int n) {
+    for (int k = h * kFusedThreads + (int)threadIdx.x; k < n; k += kAheadPerXcd * kFusedThreads) {
+      const uint4 v = ld_global16(b + k);
+      asm volatile("" ::"v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w));
+    }
+  };
+  constexpr int kUp = F * L / 8, kBranches = 2 * H * F / 8, kOut = H * F / 8, kHead = 256 * F / 8;
+  touch(a.w2_nt, kUp);
+  for (int j = 0; j < a.n_blocks; ++j) {
+    touch(a.wab_nt[j], kBranches);
+    touch(a.wo_nt[j], kOut);
+  }
+  touch(a.wh_nt, kHead);
+  if (!a.head.want_grad) return;
+  const int bytes = 16 * (kUp + a.n_blocks * (kBranches + kOut) + kHead);
+  for (int q = 0; q < bytes >> 18; ++q) __builtin_amdgcn_s_sleep(127);
+  touch(a.wh_nn, kHead);
+  for (int j = a.n_blocks - 1; j >= 0; --j) {
+    touch(a.wo_nn[j], kOut);
+    touch(a.wab_nn[j], kBranches);
+  }
+  touch(a.w2_nn, kUp);
+}
+
 template <int F, int L, int H>
 __global__ void __launch_bounds__(kFusedThreads, 1) fused_kernel(FusedArgs a) {
   typedef FusedDims<F, L, H> D;
+  if ((int)blockIdx.x >= a.row_blocks) {
+    read_weights_ahead<F, L, H>(a, ((int)blockIdx.x - a.row_blocks) >> 3);
+    return;
+  }
   constexpr int BM = D::BM, NW = D::NW, RPW = D::RPW, H2 = D::H2, LDA = D::LDA, LDF = D::LDF,
                 LDH = D::LDH;
   static_assert((H / 16) % NW == 0, "branch columns per wave");
@@ -1030,7 +1070,10 @@ static hipError_t launch_t(const FusedArgs& a, int grid_rows, hipStream_t s) {
   }
   const int blocks = (grid_rows + kFusedRows - 1) / kFusedRows;
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL((fused_kernel<F, L, H>), dim3(blocks), dim3(kFusedThreads), D::BYTES, s, a);
+  FusedArgs b = a;
+  b.row_blocks = blocks;
+  const int ahead = blocks <= kAheadMaxBlocks ? 8 * kAheadPerXcd : 0;
+  hipLaunchKernelGGL((fused_kernel<F, L, H>), dim3(blocks + ahead), dim3(kFusedThreads), D::BYTES, s, b);
   return hipGetLastError();
 }
 
