@@ -99,6 +99,7 @@ struct FusedInArgs {
   uint8_t* tgt;           // [rows]
   bf16_t* x16;            // [rows, F]
   float* x1;              // [rows, L]
+  int row_blocks;         // set by the launcher
 };
 
 // Row-block kernel after the FDM adjoint: dX = dX' W1 (adjoint of Eq. 14),
