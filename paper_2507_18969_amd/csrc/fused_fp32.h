@@ -27,8 +27,8 @@ struct FusedFp32Args {
 
 // Rows of a step that take it.  One workgroup has 16 rows and a CU's share of the
 // matrix cores, but none of the launches between the products (2 blocks of 128,
-// whole update: 8 rows 112 us as launches, 96 so; 64 rows 114 and 103; 1024 rows
-// 148 and 130; 4000 rows 285 and 227).  From 4096 rows the LayerNorm's adjoint also
+// whole update: 8 rows 109 us as launches, 92 so; 64 rows 115 and 97; 1024 rows
+// 146 and 125; 4000 rows 283 and 223).  From 4096 rows the LayerNorm's adjoint also
 // forms column sums, in another order.
 constexpr int kFusedFp32Rows = 4095;
 // F = 256, L and H multiples of 64 up to 256 and 128, 1..3 branches.

@@ -4,7 +4,7 @@
 // As launches of their own these 20 products, normalisations and the head take 3 to
 // 7 us each at a few rows, most of it launch and first loads: 80 us of a 112 us step
 // of 8 streams (2 blocks of 128).  Here the rows stay in LDS, each product's weights
-// are requested under the epilogue of the one before, and the whole takes 60 us:
+// are requested under the epilogue of the one before, and the whole takes 58 us:
 // about 25 us of products, the rest their epilogues, normalisations and the head.
 // Every sum has the order and rounding of the separate kernels: results are the same
 // bits.
@@ -153,9 +153,11 @@ struct RowProduct {
 };
 
 // One wave's 32 columns of [16, K] x W, W[k][n]: column 32 t + 2 (lane mod 16) + j
-// in acc[j], so a row's loads are a whole line; D groups of 16 k in flight.
+// in acc[j], so a row's loads are a whole line; D groups of 16 k in flight (4: 94 us
+// a step of 8 rows, 8: 98, 2: 91.5; what is requested early holds up the epilogue's
+// own accesses).
 struct ColProduct {
-  static constexpr int D = 4;
+  static constexpr int D = 2;
   uint2 r[D][4];
   __amdgpu_buffer_rsrc_t rs;
   uint32_t voff, ld;  // bytes
