@@ -755,10 +755,11 @@ edpc_status edpc_rc_encode(const uint32_t* d_cum, const uint8_t* d_sym, size_t n
     if (n_streams == 0) fail(EDPC_E_INVALID_ARG, "n_streams must be >= 1");
     if (cap < 2 * n_steps + 2) fail(EDPC_E_INVALID_ARG, "cap_per_stream < 2 * n_steps + 2");
     hipStream_t s = S(stream);
-    std::vector<uint64_t> l(n_streams);
+    std::vector<uint64_t> l;
     Scratch scratch(n_streams * 8, s);
     uint64_t* d_len = (uint64_t*)scratch.get();
     k_rc_table_encode(d_cum, d_sym, n_steps, n_streams, d_out, cap, d_len, s);
+    l.resize(n_streams);
     hip_check(hipMemcpyAsync(l.data(), d_len, n_streams * 8, hipMemcpyDeviceToHost, s), "copy");
     hip_check(hipStreamSynchronize(s), "rc encode");
     for (size_t i = 0; i < n_streams; ++i) h_out_lens[i] = (uint32_t)l[i];

@@ -971,7 +971,7 @@ void k_rc_finish(StreamIO io, int n_streams, hipStream_t s) {
 // time.  One thread per stream waits for two dependent loads a step, and as soon
 // as one of its wave's 64 streams carries, for the bytes it reads back (3000
 // streams x 40 steps: 44 to 16 us).
-__global__ void __launch_bounds__(256) rc_table_encode_kernel(
+__global__ void __launch_bounds__(256) rc_table_encode_wave_kernel(
     const uint32_t* __restrict__ cum, const uint8_t* __restrict__ sym, size_t n_steps,
     size_t n_streams, uint8_t* __restrict__ out, size_t cap, uint64_t* __restrict__ out_lens) {
   const int lane = threadIdx.x & 63;
@@ -1063,10 +1063,50 @@ __global__ void __launch_bounds__(256) rc_table_encode_kernel(
   if (lane == 0) out_lens[s] = done;
 }
 
+// The same, one thread per stream: for more streams than fill the chip with a wave
+// each (rc_wave_streams).
+__global__ void rc_table_encode_thread_kernel(
+    const uint32_t* __restrict__ cum, const uint8_t* __restrict__ sym, size_t n_steps,
+    size_t n_streams, uint8_t* __restrict__ out, size_t cap, uint64_t* __restrict__ out_lens) {
+  const size_t s = (size_t)blockIdx.x * 64 + threadIdx.x;
+  if (s >= n_streams) return;
+  RcEnc e;
+  rc_enc_init(e);
+  uint8_t* o = out + s * cap;
+  for (size_t t = 0; t < n_steps; ++t) {
+    const uint32_t* c = cum + (t * n_streams + s) * 257;
+    const uint32_t x = sym[t * n_streams + s];
+    rc_encode(e, o, cap, c[x], c[x + 1] - c[x]);
+  }
+  rc_finish(e, o, cap);
+  out_lens[s] = e.pos;
+}
+
+// Most streams that take a wave each.  8192 waves fill the chip; past that they
+// come in turn, and their time is that of the instructions they issue, 64 times
+// those of a thread per stream, whose own time is the latency of a step's
+// dependent loads whatever the number of streams.  So the line is where the issue
+// of all streams passes that latency, and it lies lower where a few steps leave
+// little latency to hide.  Whole calls, us, a thread and a wave per stream:
+//   encode  4 steps: 4000 streams 34.6 and 34.6, 8000 36.8 and 38.7, 128000 103 and 154
+//          64 steps: 6000 101 and 70, 12000 104 and 101, 16000 108 and 122, 32000 141 and 203
+//          (symbols that the tables say are likely; 10000 x 40 unlikely ones, more bytes
+//          a step: 78 and 84)
+//   decode  4 steps: 6000 35.7 and 35.9, 12000 39.8 and 44.2, 128000 114 and 190
+//          16 steps: 8000 72 and 58, 12000 74 and 70, 16000 77 and 81, 64000 155 and 241
+//          64 steps: 16000 283 and 237, 24000 349 and 329, 32000 365 and 433
+static size_t rc_wave_streams(size_t n_steps, bool decode) {
+  return n_steps < 16 ? 6000 : !decode ? 8000 : n_steps < 64 ? 12000 : 24000;
+}
+
 void k_rc_table_encode(const uint32_t* cum, const uint8_t* sym, size_t n_steps, size_t n_streams,
                        uint8_t* out, size_t cap, uint64_t* out_lens, hipStream_t s) {
-  hipLaunchKernelGGL(rc_table_encode_kernel, dim3(blocks_for(n_streams, 4)), dim3(256), 0, s, cum,
-                     sym, n_steps, n_streams, out, cap, out_lens);
+  if (n_streams <= rc_wave_streams(n_steps, false))
+    hipLaunchKernelGGL(rc_table_encode_wave_kernel, dim3(blocks_for(n_streams, 4)), dim3(256), 0, s, cum,
+                       sym, n_steps, n_streams, out, cap, out_lens);
+  else
+    hipLaunchKernelGGL(rc_table_encode_thread_kernel, dim3(blocks_for(n_streams, 64)), dim3(64), 0, s, cum,
+                       sym, n_steps, n_streams, out, cap, out_lens);
 }
 
 // Decoder with caller's tables, one wave per stream: the lanes hold the whole
@@ -1080,7 +1120,7 @@ void k_rc_table_encode(const uint32_t* cum, const uint8_t* sym, size_t n_steps, 
 // 108 to 33 us).
 constexpr int kRcAhead = 4;
 
-__global__ void __launch_bounds__(256) rc_table_decode_kernel(
+__global__ void __launch_bounds__(256) rc_table_decode_wave_kernel(
     const uint32_t* __restrict__ cum, const uint8_t* __restrict__ in,
     const uint64_t* __restrict__ in_lens, size_t cap, size_t n_steps, size_t n_streams,
     uint8_t* __restrict__ sym) {
@@ -1148,10 +1188,33 @@ __global__ void __launch_bounds__(256) rc_table_decode_kernel(
   }
 }
 
+// The same, one thread per stream, for many streams (rc_wave_streams).
+__global__ void rc_table_decode_thread_kernel(
+    const uint32_t* __restrict__ cum, const uint8_t* __restrict__ in,
+    const uint64_t* __restrict__ in_lens, size_t cap, size_t n_steps, size_t n_streams,
+    uint8_t* __restrict__ sym) {
+  const size_t s = (size_t)blockIdx.x * 64 + threadIdx.x;
+  if (s >= n_streams) return;
+  const uint8_t* p = in + s * cap;
+  const uint64_t len = in_lens[s] < cap ? in_lens[s] : cap;
+  RcDec d;
+  rc_dec_init(d, p, len);
+  for (size_t t = 0; t < n_steps; ++t) {
+    const uint32_t* c = cum + (t * n_streams + s) * 257;
+    const uint32_t x = rc_find(d, c);
+    rc_consume(d, p, len, c[x], c[x + 1]);
+    sym[t * n_streams + s] = (uint8_t)x;
+  }
+}
+
 void k_rc_table_decode(const uint32_t* cum, const uint8_t* in, const uint64_t* in_lens, size_t cap,
                        size_t n_steps, size_t n_streams, uint8_t* sym, hipStream_t s) {
-  hipLaunchKernelGGL(rc_table_decode_kernel, dim3(blocks_for(n_streams, 4)), dim3(256), 0, s, cum,
-                     in, in_lens, cap, n_steps, n_streams, sym);
+  if (n_streams <= rc_wave_streams(n_steps, true))
+    hipLaunchKernelGGL(rc_table_decode_wave_kernel, dim3(blocks_for(n_streams, 4)), dim3(256), 0, s, cum,
+                       in, in_lens, cap, n_steps, n_streams, sym);
+  else
+    hipLaunchKernelGGL(rc_table_decode_thread_kernel, dim3(blocks_for(n_streams, 64)), dim3(64), 0, s, cum,
+                       in, in_lens, cap, n_steps, n_streams, sym);
 }
 
 // CRC-32 (IEEE 802.3, reflected polynomial 0xEDB88320), one thread per stream.
