@@ -14,6 +14,8 @@ struct Kept {
 };
 constexpr size_t kKeptBytes = (size_t)64 << 20;  // all devices together
 constexpr int kKeptAge = 64;
+// A small call takes no large block: it would keep it from ageing.
+bool fits(size_t kept, size_t bytes) { return kept >= bytes && kept <= std::max(2 * bytes, (size_t)1 << 20); }
 
 struct Pool {
   std::mutex mu;
@@ -47,7 +49,7 @@ Scratch::Scratch(size_t bytes, hipStream_t s) : s_(s) {
   size_t best = pl.free.size();
   for (size_t i = 0; i < pl.free.size(); ++i) {
     ++pl.free[i].age;
-    if (pl.free[i].device == device_ && pl.free[i].bytes >= bytes &&
+    if (pl.free[i].device == device_ && fits(pl.free[i].bytes, bytes) &&
         (best == pl.free.size() || pl.free[i].bytes < pl.free[best].bytes))
       best = i;
   }
@@ -79,6 +81,18 @@ Scratch::~Scratch() {
   }
   pl.free.push_back(Kept{device_, p_, bytes_, 0});
   pl.bytes += bytes_;
+}
+
+void* device_malloc(size_t bytes) {
+  void* p = nullptr;
+  hipError_t e = hipMalloc(&p, bytes);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    scratch_give_back();
+    e = hipMalloc(&p, bytes);
+  }
+  hip_check(e, "hipMalloc");
+  return p;
 }
 
 void scratch_give_back() {

@@ -1087,7 +1087,7 @@ void Model::autotune(hipStream_t s) {
   if (bf16) {
     size_t most = 0;
     for (int t = TILE_W128x128; t < TILE_COUNT; ++t) most = std::max(most, wgrad_part_floats(t));
-    hip_check(hipMalloc(&trial.p, most * sizeof(float)), "hipMalloc");
+    trial.p = device_malloc(most * sizeof(float));
     wg_part = (float*)trial.p;
   }
   for (int ps = 0; ps < PS_COUNT; ++ps) {
