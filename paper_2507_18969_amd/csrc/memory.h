@@ -122,6 +122,7 @@ class Upload {
 // calls have not used goes back, and all of them do when an allocation of this
 // library runs out of memory or a model is made.  (Mutual information of 1024
 // samples, 8 MiB: 113 to 60 us.)
+constexpr size_t kScratchKept = (size_t)64 << 20;  // all devices together
 class Scratch {
  public:
   Scratch(size_t bytes, hipStream_t s);

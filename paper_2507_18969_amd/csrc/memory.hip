@@ -12,7 +12,6 @@ struct Kept {
   size_t bytes;
   int age;  // calls since it was last used
 };
-constexpr size_t kKeptBytes = (size_t)64 << 20;  // all devices together
 constexpr int kKeptAge = 64;
 // A small call takes no large block: it would keep it from ageing.
 bool fits(size_t kept, size_t bytes) { return kept >= bytes && kept <= std::max(2 * bytes, (size_t)1 << 20); }
@@ -75,7 +74,7 @@ Scratch::~Scratch() {
   if (hipStreamSynchronize(s_) != hipSuccess) return;  // (a failed device: nothing can be reused or freed)
   Pool& pl = pool();
   std::lock_guard<std::mutex> lk(pl.mu);
-  if (pl.bytes + bytes_ > kKeptBytes) {
+  if (pl.bytes + bytes_ > kScratchKept) {
     (void)hipFree(p_);
     return;
   }
