@@ -72,8 +72,12 @@ typedef enum { EDPC_FP32 = 0, EDPC_BF16 = 1 } edpc_precision;
 #define EDPC_CFG_ZERO_HEAD 0x1u /* head weights start at zero (with lr = 0 the
                                    model predicts exactly 1/256: a test case) */
 #define EDPC_CFG_AUTOTUNE 0x2u  /* encoder / model creation times every tile
-                                   configuration of each matrix product and
-                                   keeps the fastest; the choice is written to
+                                   configuration of each matrix product (FP32:
+                                   each matrix instruction, and each tile of
+                                   the weight gradients) and keeps the
+                                   fastest; products that run inside a
+                                   row-block kernel keep their defaults.  The
+                                   choice is written to
                                    the container (so two encodes may pick
                                    different, equally valid, summation orders).
                                    Without it a fixed default is used. */
@@ -93,12 +97,13 @@ typedef enum { EDPC_FP32 = 0, EDPC_BF16 = 1 } edpc_precision;
                                    power of two <= 256; excludes
                                    EDPC_CFG_NO_LTE.  Runs the layer-by-layer
                                    step in both precisions. */
-#define EDPC_CFG_LAYERWISE 0x10u /* BF16 models whose shape has the row-block
-                                   fused step run the layer-by-layer launch
-                                   sequence instead.  The two sequences sum in
+#define EDPC_CFG_LAYERWISE 0x10u /* models whose shape has a row-block kernel
+                                   run the layer-by-layer launch sequence
+                                   instead.  BF16: the two sequences sum in
                                    different orders; the choice is recorded in
                                    the container and the decoder follows the
-                                   container, not this flag. */
+                                   container, not this flag.  FP32: the same
+                                   results bit for bit. */
 #define EDPC_CFG_NO_GRAPHS 0x20u /* sessions launch every step directly instead
                                    of replaying captured windows of 32 steps
                                    (same results; for timing and debugging) */
@@ -239,11 +244,13 @@ void edpc_model_destroy(edpc_model* m);
 
 /* The same with an explicit kernel configuration: `kernel_id` is the 64-bit
  * id a container records (tile shape per matrix product, 4 bits per product
- * slot; bit 47 the BF16 row-block fused step; bit 46 the layer-by-layer
- * step's LayerNorm adjoint with its column sums folded in; bits 48.. the
- * numerics revision), so that a model can run the summation orders of a given
- * container, or a chosen tile everywhere.  0 picks the default.  An id of
- * another numerics revision, an unknown tile, or a tile or fused step the
+ * slot; for FP32 products but the weight gradients 0..2 mean the 16 x 16 x 4
+ * matrix instruction and 3..6 the 32 x 32 x 2 one, whose tile the library takes
+ * by size with the same results; bit 47 the BF16 row-block fused step; bit 46
+ * the layer-by-layer step's LayerNorm adjoint with its column sums folded in;
+ * bits 48.. the numerics revision), so that a model can run the summation orders
+ * of a given container, or a chosen tile everywhere.  0 picks the default.  An
+ * id of another numerics revision, an unknown tile, or a tile or fused step the
  * model's shape and precision cannot run is EDPC_E_UNSUPPORTED. */
 edpc_status edpc_model_create_with_kernels(const edpc_config* cfg, size_t n_slots,
                                            size_t max_rows, uint64_t kernel_id,

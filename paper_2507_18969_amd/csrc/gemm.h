@@ -124,11 +124,11 @@ bool wide_tile_supported(int tile, bool bf16, EpiKind epi, int nb);
 // matrices (1..3) for the gated products.
 hipError_t launch_gemm(int tile, bool bf16, bool a_kmajor, bool b_kmajor, EpiKind epi, int nb,
                        const GemmArgs& g, int grid_m_max, hipStream_t s);
-// `part`: scratch of wgrad_part_floats(tile) floats for the balanced launch of
-// wide tiles (taken when a table has at least kWgradRanges tiles), or null for
+// BF16 weight gradients.  `part`: scratch of wgrad_part_floats(tile) floats for the
+// balanced launch of wide tiles (taken when a table has at least kWgradRanges tiles), or null for
 // one work-group per tile.
-hipError_t launch_wgrad(int tile, bool bf16, const WgradProblem* d_probs, int n_probs,
-                        int total_tiles, const StepState* st, float* part, hipStream_t s);
+hipError_t launch_wgrad(int tile, const WgradProblem* d_probs, int n_probs, int total_tiles,
+                        const StepState* st, float* part, hipStream_t s);
 // The same weight gradients, BF16, with Adam in the epilogue, on tiles of edge
 // x edge (M and N multiples of 32, the shared weights of the row-block step;
 // tile_begin and tiles_n for that edge), plus elem_items work-groups of
@@ -138,13 +138,13 @@ inline int wgrad_adam_edge(int tile) { return tile >= TILE_64x64 ? 64 : 32; }
 hipError_t launch_wgrad_adam(int edge, const WgradProblem* d_probs, int n_probs, int total_tiles,
                              int elem_items, const StepState* st, const WgradAdam& ad, hipStream_t s);
 // FP32 products (gemm_fp32.hip) and wide tiles (gemm_wide.hip), reached
-// through the launchers above.
+// through the launchers above but for the FP32 weight gradients.
 hipError_t launch_gemm_fp32(int tile, bool a_kmajor, bool b_kmajor, EpiKind epi, int nb,
                             const GemmArgs& g, int grid_m_max, hipStream_t s);
-// sums: what else to sum in the launch (kernels.h), over at most max_rows rows, or null
+// sums: what else the launch sums (kernels.h), over at most max_rows rows
 struct GradSums;
 hipError_t launch_wgrad_fp32(int tile, const WgradProblem* d_probs, int n_probs, int total_tiles,
-                             const StepState* st, const GradSums* sums, int max_rows, hipStream_t s);
+                             const StepState* st, const GradSums& sums, int max_rows, hipStream_t s);
 hipError_t launch_gemm_wide(int tile, bool a_kmajor, bool b_kmajor, EpiKind epi, int nb,
                             const GemmArgs& g, int grid_m_max, hipStream_t s);
 hipError_t launch_wgrad_wide(int tile, const WgradProblem* d_probs, int n_probs, int total_tiles,

@@ -453,15 +453,11 @@ hipError_t launch_gemm_fp32(int tile, bool ak, bool bk, EpiKind epi, int nb, con
 
 template <class T>
 static hipError_t launch_w(const WgradProblem* d_probs, int n_probs, int tiles, const StepState* st,
-                           const GradSums* gs, int max_rows, hipStream_t s) {
+                           const GradSums& gs, int max_rows, hipStream_t s) {
   typedef F32Compute<T, false, false, 1> FC;
-  size_t smem = FC::SMEM;
-  int emb_blocks = 0, wgs = tiles;
-  if (gs) {
-    smem = std::max(smem, emb_lds_bytes(gs->sub_rows, gs->C, gs->E));
-    emb_blocks = (max_rows + gs->chunk_rows - 1) / gs->chunk_rows;
-    wgs += emb_blocks + gs->col_blocks * ((max_rows + kColChunk - 1) / kColChunk);
-  }
+  const size_t smem = std::max((size_t)FC::SMEM, emb_lds_bytes(gs.sub_rows, gs.C, gs.E));
+  const int emb_blocks = (max_rows + gs.chunk_rows - 1) / gs.chunk_rows;
+  const int wgs = tiles + emb_blocks + gs.col_blocks * ((max_rows + kColChunk - 1) / kColChunk);
   if (wgs == 0) return hipSuccess;
   static_assert(FC::SMEM <= 160 * 1024, "tile does not fit in LDS");
   if (smem > 64 * 1024) {
@@ -474,12 +470,12 @@ static hipError_t launch_w(const WgradProblem* d_probs, int n_probs, int tiles, 
     }
   }
   hipLaunchKernelGGL((wgrad_fp32_kernel<T>), dim3(wgs), dim3(kF32Threads), smem, s, d_probs, n_probs, tiles,
-                     emb_blocks, st, gs ? *gs : GradSums{});
+                     emb_blocks, st, gs);
   return hipGetLastError();
 }
 
 hipError_t launch_wgrad_fp32(int tile, const WgradProblem* p, int n, int tt, const StepState* st,
-                             const GradSums* gs, int max_rows, hipStream_t s) {
+                             const GradSums& gs, int max_rows, hipStream_t s) {
   switch (tile) {  // the table is laid out in tiles of this shape
     case TILE_32x32: return launch_w<T32x32>(p, n, tt, st, gs, max_rows, s);
     case TILE_64x32: return launch_w<F32Tile<16, 2, 1, 2, 2, 64, 2, 2>>(p, n, tt, st, gs, max_rows, s);

@@ -150,9 +150,8 @@ KernelConfig Model::default_config(const edpc_config& c, size_t rows) {
   const int F = c.context * c.embed, L = c.latent, H = c.hidden;
   const int KH = c.branches * H;
   const bool bf = c.precision == EDPC_BF16;
-  // tiles wanted per product: the FP32 autotuner took 32 x 32 tiles for every
-  // product at 1024 rows of the 1024-stream model (512 of them for 512
-  // outputs), where 256 tiles would give 64 x 32 (515 against 495 us a step)
+  // tiles wanted per product.  FP32: an id gives the instruction (gemm_fp32.hip takes
+  // the tile by size), 32 x 32 x 2 from 512 tiles of 64 x 64 outputs on
   const size_t want = bf ? 256 : 512;
   auto one = [&](int n) { return pick_tile(rows, {{0, n}}, want, bf); };
   k.tile[PS_LTE_DOWN] = one(L);
@@ -196,10 +195,8 @@ KernelConfig Model::default_config(const edpc_config& c, size_t rows) {
       if (wg_tiles(TILE_W256x256) >= (size_t)kWgradRanges) k.tile[PS_WGRAD] = TILE_W256x256;
       if (H <= 512) k.tile[PS_OUT] = TILE_W128x128;
     } else {
-      // FP32 (35.5 against 30.0 ms per step with the general rule): forward
-      // products on 128 x 128 tiles for at most 256 outputs, 64 x 64 when
-      // K <= 512, else 128 x 64; every input adjoint on 64 x 128; the
-      // weight gradients on 64 x 64
+      // FP32: the 32 x 32 x 2 instruction for every product (containers record the ids,
+      // so they stay what they were when an id was also the tile)
       auto fwd = [&](int n, int kk) {
         return n <= 256 ? TILE_128x128 : kk <= 512 ? TILE_64x64 : TILE_128x64;
       };
@@ -828,9 +825,11 @@ static GemmArgs ga() {
 // Whether an FP32 step on a grid of R rows takes the row-block kernel: the model
 // allows it (f32a), its sums are those of the products' tiles (the 16 x 16 x 4
 // instruction), and R is in its range.
+static constexpr ProductSlot kRowBlockProducts[] = {PS_LTE_UP,   PS_GATE,     PS_OUT, PS_HEAD,
+                                                    PS_HEAD_BWD, PS_GATE_BWD, PS_DZ,  PS_LTE_UP_BWD};
 bool Model::row_block_fp32(int R) const {
   if (!f32a.st || R > kFusedFp32Rows) return false;
-  for (int ps : {PS_LTE_UP, PS_GATE, PS_OUT, PS_HEAD, PS_HEAD_BWD, PS_GATE_BWD, PS_DZ, PS_LTE_UP_BWD})
+  for (int ps : kRowBlockProducts)
     if (kc.tile[ps] > TILE_32x64) return false;
   return true;
 }
@@ -894,10 +893,12 @@ void Model::product(int ps, int j, int R, hipStream_t s) {
       g.A = bf16 ? (const void*)dX1_16 : (const void*)dX1_32; g.lda = L;
       g.B = W_("w1"); g.ldb = F; g.N = F; g.K = L; g.out32 = dX; g.ld_out32 = F;
       return gemm(ps, true, false, EPI_STORE, 1, g, R, s);
-    case PS_WGRAD: {
-      const WgTable& t = wg_tab[kc.tile[PS_WGRAD]];
-      TIMED(PS_WGRAD, hip_check(launch_wgrad(kc.tile[PS_WGRAD], bf16, t.d, t.n, t.tiles, st,
-                                             wg_part, s),
+    case PS_WGRAD: {  // (FP32: with the embedding gradient's and the column sums' first pass)
+      const int id = kc.tile[PS_WGRAD];
+      const WgTable& t = wg_tab[id];
+      const GradSums gs{d_cs, n_cs, cs_blocks, cs_cols, cs_partial, ctx, dX, C, E, emb_chunk, emb_sub, emb_partial};
+      TIMED(PS_WGRAD, hip_check(bf16 ? launch_wgrad(id, t.d, t.n, t.tiles, st, wg_part, s)
+                                     : launch_wgrad_fp32(id, t.d, t.n, t.tiles, st, gs, R, s),
                                 "wgrad launch"));
       return;
     }
@@ -1040,16 +1041,9 @@ void Model::step(StepMode mode, const StreamIO& io, const StepOutputs& out, int 
   if (low_rank)
     TIMED(KC_FDM_BWD, k_fdm_bwd(st, X32, dX1_32, A, mA, vA, nullptr, slot, F, L, ac, out.update,
                                 dX, nullptr, R, s));
-  if (bf16) {
-    TIMED(KC_EMB_GRAD, k_emb_grad_partial(st, ctx, dX, C, E, emb_partial, emb_chunk, emb_sub, R, s));
-    product(PS_WGRAD, 0, R, s);
-    TIMED(KC_COLSUM, k_colsum_partial(st, d_cs, n_cs, cs_blocks, cs_cols, cs_partial, R, s));
-  } else {
-    const GradSums gs{d_cs, n_cs, cs_blocks, cs_cols, cs_partial, ctx, dX, C, E, emb_chunk, emb_sub, emb_partial};
-    const WgTable& t = wg_tab[kc.tile[PS_WGRAD]];
-    TIMED(PS_WGRAD, hip_check(launch_wgrad_fp32(kc.tile[PS_WGRAD], t.d, t.n, t.tiles, st, &gs, R, s),
-                              "wgrad launch"));
-  }
+  if (bf16) TIMED(KC_EMB_GRAD, k_emb_grad_partial(st, ctx, dX, C, E, emb_partial, emb_chunk, emb_sub, R, s));
+  product(PS_WGRAD, 0, R, s);
+  if (bf16) TIMED(KC_COLSUM, k_colsum_partial(st, d_cs, n_cs, cs_blocks, cs_cols, cs_partial, R, s));
   if (out.update) {
     TIMED(KC_ADAM, k_adam(st, param, grad, m, v, p16, P, ac, d_kind, d_part_jobs, s));
   } else {
@@ -1059,11 +1053,13 @@ void Model::step(StepMode mode, const StreamIO& io, const StepOutputs& out, int 
   hip_check(hipGetLastError(), "step launch");
 }
 
-// Time every tile configuration of every product on the model's own buffers
-// (rows = max_rows) and keep the fastest.  Outputs of the trial launches are
+// Time every tile configuration of every product (FP32: every instruction, and every
+// tile of the weight gradients) on the model's own buffers (rows = max_rows) and keep
+// the fastest.  Outputs of the trial launches are
 // scratch: every buffer they write is rewritten by the first real step.
 void Model::autotune(hipStream_t s) {
   const int R = (int)max_rows;
+  const bool row_block = row_block_fp32(R);
   k_step_explicit(st, R, 1, cfg.beta1, cfg.beta2, s);
   hipEvent_t e0, e1;
   hip_check(hipEventCreate(&e0), "event");
@@ -1101,14 +1097,25 @@ void Model::autotune(hipStream_t s) {
     // 128 x 128 tile timed best here but took 45 against 34 us with Adam (112
     // work-groups move the Adam traffic).  It keeps its default.
     if (ps == PS_WGRAD && kc.fused) continue;
-    int best = kc.tile[ps];
+    // FP32 row-block kernel: faster than its products' launches over its whole range,
+    // so they keep the instruction that it needs
+    if (row_block && std::find(std::begin(kRowBlockProducts), std::end(kRowBlockProducts), ps) !=
+                         std::end(kRowBlockProducts))
+      continue;
+    const int given = kc.tile[ps];
+    int best = given;
     float best_ms = 1e30f;
     const EpiKind epi = ps == PS_GATE ? EPI_GATE_FWD : ps == PS_GATE_BWD ? EPI_GATE_BWD : EPI_STORE;
     const int nb = ps == PS_GATE ? K : 1;
     for (int t = 0; t < TILE_COUNT; ++t) {
       const TileShape sh = tile_shape(t);
       if (!wide_tile_supported(t, bf16, epi, nb)) continue;
-      if (ps != PS_WGRAD && sh.bm > 2 * R && t != TILE_32x32) continue;
+      // FP32 products but the weight gradients: an id is an instruction (gemm_fp32.hip),
+      // so one id of each is tried, the given one for its own
+      if (!bf16 && ps != PS_WGRAD && t != given &&
+          t != (given < TILE_64x64 ? TILE_64x64 : TILE_32x32))
+        continue;
+      if (ps != PS_WGRAD && sh.bm > 2 * R && t != TILE_32x32 && t != given) continue;
       kc.tile[ps] = t;
       product(ps, 0, R, s);  // warm-up (first launch may set attributes)
       hip_check(hipEventRecord(e0, s), "event");
