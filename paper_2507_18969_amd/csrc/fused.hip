@@ -1,6 +1,7 @@
 // Row-block fused step (BF16 operands, FP32 accumulation); see fused.h.
 #include "fused.h"
 #include "head_row.h"
+#include "lds_limit.h"
 
 namespace edpc {
 
@@ -1068,13 +1069,8 @@ bool fused_supported(int F, int L, int H, int branches, int blocks) {
 template <int F, int L, int H>
 static hipError_t launch_t(const FusedArgs& a, int grid_rows, hipStream_t s) {
   typedef FusedDims<F, L, H> D;
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)fused_kernel<F, L, H>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)D::BYTES);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static LdsLimit lds;
+  if (const hipError_t e = lds.raise((const void*)fused_kernel<F, L, H>, (int)D::BYTES); e != hipSuccess) return e;
   const int blocks = (grid_rows + kFusedRows - 1) / kFusedRows;
   if (blocks == 0) return hipSuccess;
   FusedArgs b = a;

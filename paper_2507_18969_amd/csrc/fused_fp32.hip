@@ -13,6 +13,7 @@
 #include <algorithm>
 
 #include "head_row.h"
+#include "lds_limit.h"
 
 namespace edpc {
 
@@ -551,10 +552,9 @@ hipError_t launch_fused_fp32(FusedFp32Args a, int branches, const StreamIO& io, 
   void (*kernel)(FusedFp32Args, StreamIO) = branches == 1   ? fused_fp32_kernel<1>
                                             : branches == 2 ? fused_fp32_kernel<2>
                                                             : fused_fp32_kernel<3>;
-  if (smem > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-  }
+  static LdsLimit lds[3];
+  if (smem > 64 * 1024)
+    if (const hipError_t e = lds[branches - 1].raise((const void*)kernel, kLdsBytes); e != hipSuccess) return e;
   hipLaunchKernelGGL(kernel, grid, dim3(kThreads), smem, s, a, io);
   return hipGetLastError();
 }

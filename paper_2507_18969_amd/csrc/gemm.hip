@@ -2,6 +2,7 @@
 // contract, gemm_fp32.hip for the FP32 products, gemm_wide.hip for the wide
 // tiles.
 #include "gemm_epi.h"
+#include "lds_limit.h"
 
 namespace edpc {
 
@@ -328,13 +329,8 @@ static hipError_t launch_one(const GemmArgs& g, int grid_m_max, hipStream_t s) {
   constexpr int smem = TC::smem_bytes();
   static_assert(smem <= 160 * 1024, "tile does not fit in LDS");
   if constexpr (smem > 64 * 1024) {
-    static bool done = false;
-    if (!done) {
-      hipError_t e = hipFuncSetAttribute((const void*)gemm_kernel<T, AK, BKM, EPI, NB>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-      if (e != hipSuccess) return e;
-      done = true;
-    }
+    static LdsLimit lds;
+    if (const hipError_t e = lds.raise((const void*)gemm_kernel<T, AK, BKM, EPI, NB>, smem); e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((gemm_kernel<T, AK, BKM, EPI, NB>), grid, dim3(kThreads), smem, s, g);
   return hipGetLastError();
@@ -389,13 +385,8 @@ static hipError_t launch_w(const WgradProblem* d_probs, int n_probs, int total_t
   constexpr int smem = TC::smem_bytes();
   static_assert(smem <= 160 * 1024, "tile does not fit in LDS");
   if constexpr (smem > 64 * 1024) {
-    static bool done = false;
-    if (!done) {
-      hipError_t e = hipFuncSetAttribute((const void*)wgrad_kernel<T>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-      if (e != hipSuccess) return e;
-      done = true;
-    }
+    static LdsLimit lds;
+    if (const hipError_t e = lds.raise((const void*)wgrad_kernel<T>, smem); e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((wgrad_kernel<T>), dim3(total_tiles), dim3(kThreads), smem, s,
                      d_probs, n_probs, st);

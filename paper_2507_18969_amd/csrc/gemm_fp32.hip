@@ -12,6 +12,7 @@
 // adjoint 780 to 677.  The LDS reads are next: 4-byte operands for every step.
 #include "gemm_epi.h"
 #include "grad_sums.h"
+#include "lds_limit.h"
 
 #include <algorithm>
 
@@ -385,13 +386,8 @@ static hipError_t launch_one(const GemmArgs& g, int grid_m_max, hipStream_t s) {
   if (grid.x == 0 || grid.y == 0) return hipSuccess;
   static_assert(FC::SMEM <= 160 * 1024, "tile does not fit in LDS");
   if constexpr (FC::SMEM > 64 * 1024) {
-    static bool done = false;
-    if (!done) {
-      hipError_t e = hipFuncSetAttribute((const void*)gemm_fp32_kernel<T, AK, BKM, EPI, NB>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, FC::SMEM);
-      if (e != hipSuccess) return e;
-      done = true;
-    }
+    static LdsLimit lds;
+    if (const hipError_t e = lds.raise((const void*)gemm_fp32_kernel<T, AK, BKM, EPI, NB>, FC::SMEM); e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((gemm_fp32_kernel<T, AK, BKM, EPI, NB>), grid, dim3(kF32Threads), FC::SMEM, s, g);
   return hipGetLastError();
@@ -461,13 +457,8 @@ static hipError_t launch_w(const WgradProblem* d_probs, int n_probs, int tiles, 
   if (wgs == 0) return hipSuccess;
   static_assert(FC::SMEM <= 160 * 1024, "tile does not fit in LDS");
   if (smem > 64 * 1024) {
-    static bool done = false;
-    if (!done) {
-      hipError_t e = hipFuncSetAttribute((const void*)wgrad_fp32_kernel<T>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      if (e != hipSuccess) return e;
-      done = true;
-    }
+    static LdsLimit lds;
+    if (const hipError_t e = lds.raise((const void*)wgrad_fp32_kernel<T>, kLdsBytes); e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((wgrad_fp32_kernel<T>), dim3(wgs), dim3(kF32Threads), smem, s, d_probs, n_probs, tiles,
                      emb_blocks, st, gs);

@@ -13,6 +13,7 @@
 // in increasing order, each chunk by the MFMA's fixed order; fixed by the
 // tile id, which the container records.
 #include "gemm.h"
+#include "lds_limit.h"
 
 namespace edpc {
 
@@ -554,13 +555,8 @@ static hipError_t launch_wide_one(const GemmArgs& g, int grid_m_max, hipStream_t
   dim3 grid((g.N + cols - 1) / cols, (grid_m_max + T::BM - 1) / T::BM);
   if (grid.x == 0 || grid.y == 0) return hipSuccess;
   static_assert(T::SMEM <= 160 * 1024, "tile does not fit in LDS");
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_wide_kernel<T, AK, BKM, EPI>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, T::SMEM);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static LdsLimit lds;
+  if (const hipError_t e = lds.raise((const void*)gemm_wide_kernel<T, AK, BKM, EPI>, T::SMEM); e != hipSuccess) return e;
   hipLaunchKernelGGL((gemm_wide_kernel<T, AK, BKM, EPI>), grid, dim3(kWideThreads), T::SMEM, s, g);
   return hipGetLastError();
 }
@@ -609,16 +605,10 @@ template <class T>
 static hipError_t launch_wgrad_wide_t(const WgradProblem* d_probs, int n_probs, int total_tiles,
                                       const StepState* st, float* part, hipStream_t s) {
   if (total_tiles == 0) return hipSuccess;
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)wgrad_wide_kernel<T>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, T::SMEM);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)wgrad_wide_split_kernel<T>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, T::SMEM);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static LdsLimit whole, split;
+  hipError_t e = whole.raise((const void*)wgrad_wide_kernel<T>, T::SMEM);
+  if (e == hipSuccess) e = split.raise((const void*)wgrad_wide_split_kernel<T>, T::SMEM);
+  if (e != hipSuccess) return e;
   if (part && total_tiles >= kWgradRanges) {
     hipLaunchKernelGGL((wgrad_wide_split_kernel<T>), dim3(kWgradRanges), dim3(kWideThreads), T::SMEM,
                        s, d_probs, n_probs, st, total_tiles, part);
