@@ -327,6 +327,18 @@ void edpc_model_destroy(edpc_model* m) {
   delete m;
 }
 
+// Whether p is memory of the current device, which any kernel may read.  A copy takes
+// other memory as well (the host's, another GPU's) or refuses it; a kernel faults.
+static bool on_this_device(const void* p) {
+  hipPointerAttribute_t a;
+  int dev = 0;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == dev;
+}
+
 edpc_status edpc_model_step(edpc_model* mh, const uint8_t* d_ctx, const uint8_t* d_target,
                             const uint32_t* h_slot, size_t rows, float* d_probs, uint32_t* d_cum,
                             float* d_loss, uint32_t flags, void* stream) {
@@ -357,13 +369,13 @@ edpc_status edpc_model_step(edpc_model* mh, const uint8_t* d_ctx, const uint8_t*
     if (out.keep_fdm_grad)  // slots outside this call get a zero gradient
       hip_check(hipMemsetAsync(m.dUkeep, 0, m.n_slots * (size_t)m.L * m.L * sizeof(float), s), "memset");
     const uint32_t tau = out.update ? (uint32_t)(m.tau + 1) : (uint32_t)(m.tau > 0 ? m.tau : 1);
-    if (rows <= (size_t)kInlineSlots) {
+    if (rows <= (size_t)kInlineSlots && on_this_device(d_ctx) && (!d_target || on_this_device(d_target))) {
       InlineSlots in;
       std::memcpy(in.v, h_slot, rows * sizeof(uint32_t));
       k_stage(m.st, (int)rows, tau, m.cfg.beta1, m.cfg.beta2, d_ctx, m.ctx, m.C, d_target, m.tgt, in, m.slot, s);
     } else {
-      hip_check(hipMemcpyAsync(m.ctx, d_ctx, rows * m.C, hipMemcpyDeviceToDevice, s), "copy");
-      if (d_target) hip_check(hipMemcpyAsync(m.tgt, d_target, rows, hipMemcpyDeviceToDevice, s), "copy");
+      hip_check(hipMemcpyAsync(m.ctx, d_ctx, rows * m.C, hipMemcpyDefault, s), "copy");
+      if (d_target) hip_check(hipMemcpyAsync(m.tgt, d_target, rows, hipMemcpyDefault, s), "copy");
       hip_check(hipMemcpyAsync(m.slot, h_slot, rows * sizeof(uint32_t), hipMemcpyHostToDevice, s), "copy");
       k_step_explicit(m.st, (int)rows, tau, m.cfg.beta1, m.cfg.beta2, s);
     }
