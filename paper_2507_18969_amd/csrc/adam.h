@@ -23,11 +23,7 @@ __device__ __forceinline__ void adam1(float& P, float& M, float& V, float g, flo
 __device__ __forceinline__ void adam8_math(float P[8], float M[8], float V[8], const float gv[8],
                                            float lr_bc, float inv_bc2, const AdamCfg& ac) {
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    M[k] = ac.beta1 * M[k] + (1.0f - ac.beta1) * gv[k];
-    V[k] = ac.beta2 * V[k] + (1.0f - ac.beta2) * gv[k] * gv[k];
-    P[k] = P[k] - lr_bc * M[k] / (sqrtf(V[k] * inv_bc2) + ac.eps);
-  }
+  for (int k = 0; k < 8; ++k) adam1(P[k], M[k], V[k], gv[k], lr_bc, inv_bc2, ac);
 }
 
 typedef float f32v4 __attribute__((ext_vector_type(4)));

@@ -48,10 +48,12 @@ __device__ __forceinline__ float adam_bias_correction(float beta, uint32_t tau) 
 __device__ __forceinline__ float gelu_f(float x) {
   return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f));
 }
+// (The rounding of the sum is written out: kernels with the same sums share it.)
 __device__ __forceinline__ float gelu_grad_f(float x) {
+#pragma clang fp contract(off)
   const float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
   const float pdf = expf(-0.5f * x * x) * 0.39894228040143268f;
-  return cdf + x * pdf;
+  return fmaf(x, pdf, cdf);
 }
 
 // Fixed-order wave reductions: a butterfly over the 64 lanes at distances 32, 16,

@@ -14,6 +14,7 @@
 
 #include "head_row.h"
 #include "lds_limit.h"
+#include "ln_row.h"
 
 namespace edpc {
 
@@ -23,8 +24,6 @@ constexpr int kWaves = 8, kThreads = 64 * kWaves;
 constexpr int kRows = 16;
 constexpr int kF = 256;          // features: one float4 a lane and row
 constexpr int kLdRow = kF + 4;   // row-major LDS rows
-
-typedef float f32q __attribute__((ext_vector_type(4)));
 
 // Accesses to rows [0, rows) of an array, `bytes` in all, at byte offset `at` (+
 // soff within the row): past the end they go nowhere and read zeros.
@@ -252,7 +251,7 @@ __global__ void __launch_bounds__(kThreads) fused_fp32_kernel(FusedFp32Args a, S
   RowProduct<NB> gt;
   ColProduct bw;
   constexpr int kHalf = 128;  // the second 16 columns of a wave lie so far on
-  static_assert(kF == 2 * kHalf && kWaves * 16 == kHalf, "two times 16 columns a wave");
+  static_assert(kF == kLnRow && kF == 2 * kHalf && kWaves * 16 == kHalf, "two times 16 columns a wave");
 
   fw.start(a.w2, L, wave, kWaves, kHalf * L);
   for (int k = threadIdx.x; k < kRows * L; k += kThreads) {
@@ -290,23 +289,15 @@ __global__ void __launch_bounds__(kThreads) fused_fp32_kernel(FusedFp32Args a, S
   }
   lds_barrier();
   for (int j = 0; j < N; ++j) {
-    {  // LayerNorm: the rounding of every sum as in the row kernel (kernels.hip)
-#pragma clang fp contract(off)
+    {  // LayerNorm
       const int lane = here() & 63;
 #pragma unroll
       for (int v = 0; v < 2; ++v) {
-        const f32q x = *(const f32q*)(sH + (wave + kWaves * v) * kLdRow + 4 * lane);
-        const float mu = wave_sum(0.f + ((x[0] + x[1]) + (x[2] + x[3]))) / (float)kF;
-        const f32q d = x - mu;
-        const float qq = fmaf(d[0], d[0], d[1] * d[1]) + fmaf(d[2], d[2], d[3] * d[3]);
-        const float var = wave_sum(0.f + qq) / (float)kF;
-        const float rs = 1.0f / sqrtf(var + 1e-5f);
-        f32q z;
+        float mu, rs;
+        const f32q z =
+            ln_row_fwd(*(const f32q*)(sH + (wave + kWaves * v) * kLdRow + 4 * lane), gm, bt, &mu, &rs);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          z[e] = fmaf(d[e] * rs, gm[e], bt[e]);
-          q[frag_at(wave + kWaves * v, 4 * lane + e)] = z[e];
-        }
+        for (int e = 0; e < 4; ++e) q[frag_at(wave + kWaves * v, 4 * lane + e)] = z[e];
         put4(a.z.of(j), bF, row_at(v, lane), z);
         if (row_of(v) < rows && lane == 0) {
           a.mean.of(j)[row_of(v)] = mu;
@@ -440,18 +431,13 @@ __global__ void __launch_bounds__(kThreads) fused_fp32_kernel(FusedFp32Args a, S
         float o[NB][2];
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-          float x[NB], prod = 1.0f, dp;
+          float x[NB], prod = 1.0f;
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
             x[b] = c ? v[e][b].y : v[e][b].x;
             prod = b == 0 ? x[b] : prod * x[b];
           }
-          {
-#pragma clang fp contract(off)
-            const float cdf = 0.5f * (1.0f + erff(prod * 0.70710678118654752f));
-            const float pdf = expf(-0.5f * prod * prod) * 0.39894228040143268f;
-            dp = acc[c][e] * fmaf(prod, pdf, cdf);
-          }
+          const float dp = acc[c][e] * gelu_grad_f(prod);
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
             o[b][c] = dp;
@@ -496,22 +482,13 @@ __global__ void __launch_bounds__(kThreads) fused_fp32_kernel(FusedFp32Args a, S
       }
     }
     lds_barrier();
-    {  // LayerNorm's adjoint, rounded as in the row kernel; -> sH and q
-#pragma clang fp contract(off)
+    {  // LayerNorm's adjoint; -> sH and q
       const int lane = here() & 63;
 #pragma unroll
       for (int v = 0; v < 2; ++v) {
         const int m = wave + kWaves * v;
-        const f32q d = *(const f32q*)(p + m * kLdRow + 4 * lane);
-        const f32q dn = *(const f32q*)(sH + m * kLdRow + 4 * lane);
-        const f32q xh = (x[v] - mu[v]) * rs[v], dx = d * gm;
-        const float s1 = fmaf(d[1], gm[1], dx[0]) + fmaf(d[2], gm[2], dx[3]);
-        const float s2 = fmaf(xh[0], dx[0], xh[1] * dx[1]) + fmaf(xh[2], dx[2], xh[3] * dx[3]);
-        const float m1 = wave_sum(0.f + s1) / (float)kF, m2 = wave_sum(0.f + s2) / (float)kF;
-        f32q o;
-        o[0] = fmaf(rs[v], fmaf(-xh[0], m2, dx[0] - m1), dn[0]);
-#pragma unroll
-        for (int e = 1; e < 4; ++e) o[e] = fmaf(rs[v], fmaf(-xh[e], m2, fmaf(d[e], gm[e], -m1)), dn[e]);
+        const f32q o = ln_row_bwd(x[v], mu[v], rs[v], gm, *(const f32q*)(p + m * kLdRow + 4 * lane),
+                                  *(const f32q*)(sH + m * kLdRow + 4 * lane));
         *(f32q*)(sH + m * kLdRow + 4 * lane) = o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) q[frag_at(m, 4 * lane + e)] = o[e];

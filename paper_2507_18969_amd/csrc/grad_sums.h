@@ -178,7 +178,7 @@ __device__ __forceinline__ void colsum_block(const StepState* __restrict__ st,
 #pragma unroll 4
       for (int r = r0 + slice; r < r1; r += 4) {
         const float xh = (h[(size_t)r * jb.ld + lc] - mean[r]) * rstd[r];
-        acc += src[(size_t)r * jb.ld + lc] * xh;
+        acc = fmaf(src[(size_t)r * jb.ld + lc], xh, acc);
       }
     } else {
 #pragma unroll 4

@@ -2,6 +2,7 @@
 #include "adam.h"
 #include "grad_sums.h"
 #include "head_row.h"
+#include "ln_row.h"
 
 #include <algorithm>
 
@@ -215,6 +216,9 @@ __global__ void __launch_bounds__(256) fdm_fwd_kernel(const StepState* __restric
   __syncthreads();
   const float* Us = U + (size_t)slot[r] * Lin * Lout;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto add = [&](float xv, float4 u) {
+    acc = make_float4(fmaf(xv, u.x, acc.x), fmaf(xv, u.y, acc.y), fmaf(xv, u.z, acc.z), fmaf(xv, u.w, acc.w));
+  };
   if (g < G) {
     // rows l = g, g + G, ... in order; loads issued kFdmBatch rows at a time
     int l = g;
@@ -224,20 +228,12 @@ __global__ void __launch_bounds__(256) fdm_fwd_kernel(const StepState* __restric
       for (int q = 0; q < kFdmBatch; ++q) u[q] = load4<NT>(Us + (size_t)(l + q * G) * Lout + 4 * t);
 #pragma unroll
       for (int q = 0; q < kFdmBatch; ++q) {
-        const float xv = xs[l + q * G];
-        acc.x += xv * u[q].x;
-        acc.y += xv * u[q].y;
-        acc.z += xv * u[q].z;
-        acc.w += xv * u[q].w;
+        add(xs[l + q * G], u[q]);
       }
     }
     for (; l < Lin; l += G) {
       const float4 u = load4<NT>(Us + (size_t)l * Lout + 4 * t);
-      const float xv = xs[l];
-      acc.x += xv * u.x;
-      acc.y += xv * u.y;
-      acc.z += xv * u.z;
-      acc.w += xv * u.w;
+      add(xs[l], u);
     }
     *(float4*)(part + g * Lout + 4 * t) = acc;
   }
@@ -283,13 +279,12 @@ __global__ void __launch_bounds__(256) fdm_bwd_kernel(
   if (g >= G) return;
   const size_t base_s = (size_t)slot[r] * Lin * Lout;
   const float4 d4 = *(const float4*)(ds + 4 * t);
-  const float b1 = ac.beta1, b2 = ac.beta2;
   const float lr_bc = ac.lr / st->bc1;
   const float inv_bc2 = 1.0f / st->bc2;
   // one row l of U_s: dx'[l] (from U before the update), dU, Adam
   auto row = [&](int l, float4 u, float4 m, float4 v) {
     const size_t idx = base_s + (size_t)l * Lout + 4 * t;
-    float part = u.x * d4.x + u.y * d4.y + u.z * d4.z + u.w * d4.w;
+    float part = fmaf(u.w, d4.w, fmaf(u.z, d4.z, fmaf(u.x, d4.x, u.y * d4.y)));
     for (int o = tpr >> 1; o >= 1; o >>= 1) part += __shfl_xor(part, o, 64);
     if (t == 0) {
       if (dx1_32) dx1_32[(size_t)r * Lin + l] = part;
@@ -303,11 +298,7 @@ __global__ void __launch_bounds__(256) fdm_bwd_kernel(
       float* mp = (float*)&m;
       float* vp = (float*)&v;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        mp[j] = b1 * mp[j] + (1.0f - b1) * gr[j];
-        vp[j] = b2 * vp[j] + (1.0f - b2) * gr[j] * gr[j];
-        up[j] -= lr_bc * mp[j] / (sqrtf(vp[j] * inv_bc2) + ac.eps);
-      }
+      for (int j = 0; j < 4; ++j) adam1<true>(up[j], mp[j], vp[j], gr[j], lr_bc, inv_bc2, ac);
       store4<NTU>(U + idx, u);
       store4<NTM>(mU + idx, m);
       store4<NTM>(vU + idx, v);
@@ -398,7 +389,31 @@ __global__ void __launch_bounds__(256) ln_fwd_kernel(const StepState* __restrict
   }
 }
 
-// Register-resident variant for F = 256 * NV: each lane holds NV float4.
+// Rows of 256 (ln_row.h).
+__global__ void __launch_bounds__(256) ln_fwd_256_kernel(const StepState* __restrict__ st,
+                                                         const float* __restrict__ h,
+                                                         const float* __restrict__ gamma,
+                                                         const float* __restrict__ beta,
+                                                         float* __restrict__ z32,
+                                                         bf16_t* __restrict__ z16,
+                                                         float* __restrict__ mean,
+                                                         float* __restrict__ rstd) {
+  const int lane = threadIdx.x & 63;
+  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= st->rows) return;
+  const size_t o = (size_t)r * kLnRow + 4 * lane;
+  float mu, rs;
+  const f32q z = ln_row_fwd(*(const f32q*)(h + o), *(const f32q*)(gamma + 4 * lane),
+                            *(const f32q*)(beta + 4 * lane), &mu, &rs);
+  if (lane == 0) {
+    mean[r] = mu;
+    rstd[r] = rs;
+  }
+  if (z32) *(f32q*)(z32 + o) = z;
+  if (z16) *(ushort4*)(z16 + o) = make_ushort4(f2bf(z[0]), f2bf(z[1]), f2bf(z[2]), f2bf(z[3]));
+}
+
+// Register-resident variant for F = 256 * NV, NV > 1: each lane holds NV float4.
 template <int NV>
 __global__ void __launch_bounds__(256) ln_fwd_reg_kernel(const StepState* __restrict__ st,
                                                          const float* __restrict__ h,
@@ -453,7 +468,7 @@ void k_ln_fwd(const StepState* st, const float* h, const float* gamma, const flo
               float* z32, bf16_t* z16, float* mean, float* rstd, int max_rows, hipStream_t s) {
   const dim3 g(blocks_for(max_rows, 4)), b(256);
   switch (F % 256 == 0 ? F / 256 : 0) {
-    case 1: hipLaunchKernelGGL(ln_fwd_reg_kernel<1>, g, b, 0, s, st, h, gamma, beta, z32, z16, mean, rstd); return;
+    case 1: hipLaunchKernelGGL(ln_fwd_256_kernel, g, b, 0, s, st, h, gamma, beta, z32, z16, mean, rstd); return;
     case 2: hipLaunchKernelGGL(ln_fwd_reg_kernel<2>, g, b, 0, s, st, h, gamma, beta, z32, z16, mean, rstd); return;
     case 4: hipLaunchKernelGGL(ln_fwd_reg_kernel<4>, g, b, 0, s, st, h, gamma, beta, z32, z16, mean, rstd); return;
     case 8: hipLaunchKernelGGL(ln_fwd_reg_kernel<8>, g, b, 0, s, st, h, gamma, beta, z32, z16, mean, rstd); return;
@@ -501,6 +516,21 @@ __global__ void __launch_bounds__(256) ln_bwd_kernel(
     if (dh16)
       *(ushort4*)(dh16 + (size_t)r * F + f) = make_ushort4(f2bf(o.x), f2bf(o.y), f2bf(o.z), f2bf(o.w));
   }
+}
+
+// Rows of 256 (ln_row.h).
+__global__ void __launch_bounds__(256) ln_bwd_256_kernel(
+    const StepState* __restrict__ st, const float* __restrict__ h, const float* __restrict__ mean,
+    const float* __restrict__ rstd, const float* __restrict__ gamma, const float* __restrict__ dz,
+    const float* __restrict__ dh_next, float* __restrict__ dh32, bf16_t* __restrict__ dh16) {
+  const int lane = threadIdx.x & 63;
+  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= st->rows) return;
+  const size_t o = (size_t)r * kLnRow + 4 * lane;
+  const f32q v = ln_row_bwd(*(const f32q*)(h + o), mean[r], rstd[r], *(const f32q*)(gamma + 4 * lane),
+                            *(const f32q*)(dz + o), *(const f32q*)(dh_next + o));
+  *(f32q*)(dh32 + o) = v;
+  if (dh16) *(ushort4*)(dh16 + o) = make_ushort4(f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3]));
 }
 
 template <int NV>
@@ -635,7 +665,7 @@ void k_ln_bwd(const StepState* st, const float* h, const float* mean, const floa
   }
   const dim3 g(blocks_for(max_rows, 4)), b(256);
   switch (F % 256 == 0 ? F / 256 : 0) {
-    case 1: hipLaunchKernelGGL(ln_bwd_reg_kernel<1>, g, b, 0, s, st, h, mean, rstd, gamma, dz, dh_next, dh32, dh16); return;
+    case 1: hipLaunchKernelGGL(ln_bwd_256_kernel, g, b, 0, s, st, h, mean, rstd, gamma, dz, dh_next, dh32, dh16); return;
     case 2: hipLaunchKernelGGL(ln_bwd_reg_kernel<2>, g, b, 0, s, st, h, mean, rstd, gamma, dz, dh_next, dh32, dh16); return;
     case 4: hipLaunchKernelGGL(ln_bwd_reg_kernel<4>, g, b, 0, s, st, h, mean, rstd, gamma, dz, dh_next, dh32, dh16); return;
     case 8: hipLaunchKernelGGL(ln_bwd_reg_kernel<8>, g, b, 0, s, st, h, mean, rstd, gamma, dz, dh_next, dh32, dh16); return;
