@@ -61,11 +61,12 @@ __device__ __forceinline__ void embed_row(const uint8_t* bytes, const float* __r
   }
 }
 
-// A workgroup takes `per` rows with n threads each: one row from 1024 features on, as
-// many as fit below (one row there leaves most threads idle: a BF16 prediction of
-// 100000 rows of 64 features 279 us, 259 so, of 256 features 433 and 418; a thread per
-// 4 features over all rows is no faster and takes 163 us against 160 at 8000 rows of
-// 4096).
+// A workgroup takes `per` rows with n threads each: one row, or from 2048 rows on as
+// many as fit (below 1024 features one row leaves threads idle, which costs nothing
+// while there are CUs to spare: a BF16 prediction of 100000 rows of 64 features 279 us,
+// 259 so, of 256 features 433 and 418; 7 rows of 256 44.9 us, 45.1 together.  A thread
+// per 4 features over all rows is no faster and takes 163 us against 160 at 8000 rows
+// of 4096).
 __global__ void __launch_bounds__(256) embed_kernel(const StepState* __restrict__ st,
                                                     const uint8_t* __restrict__ ctx,
                                                     const float* __restrict__ emb, int C, int E, int per, int n,
@@ -77,7 +78,7 @@ __global__ void __launch_bounds__(256) embed_kernel(const StepState* __restrict_
 
 void k_embed(const StepState* st, const uint8_t* ctx, const float* emb, int C, int E, float* x32,
              bf16_t* x16, int max_rows, hipStream_t s) {
-  const int n = std::min(256, C * E / 4), per = 256 / n;
+  const int n = max_rows < 2048 ? 256 : std::min(256, C * E / 4), per = 256 / n;
   hipLaunchKernelGGL(embed_kernel, dim3(blocks_for(max_rows, per)), dim3(256), 0, s, st, ctx, emb, C, E, per, n,
                      x32, x16);
 }
