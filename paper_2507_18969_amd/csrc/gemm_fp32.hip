@@ -428,11 +428,13 @@ hipError_t launch_gemm_fp32(int tile, bool ak, bool bk, EpiKind epi, int nb, con
     return (long long)((gm + t - 1) / t) * ((g.N + t - 1) / t);
   };
   if (tile < TILE_64x64) {
-    // Few tiles: one wave of products a work-group, on as many CUs as there
-    // are 16 x 16 blocks, reads less per CU (8 rows, gated K 256: 6.3 against
-    // 6.7; 333 rows, 128 outputs of K 512, 44 tiles: 5.9 against 6.6; at 176
-    // tiles 5.8 against 5.1, at 512 tiles 17.6 against 9.8).
-    if (tiles(32) < 128) return bk ? launch_fwd<T16x16>(epi, nb, g, gm, s) : launch_adj<T16x16>(epi, g, gm, s);
+    // As long as the 16 x 16 blocks have a CU each (64 tiles of 32 x 32), one wave of
+    // products a work-group reads less per CU; past that CUs share two and the larger
+    // tile, with half the operands a product, is the better one.  All products of
+    // steps of 16 to 640 rows, time of 16 x 16 over 32 x 32: 16 to 64 tiles 0.94 (gated
+    // K 512 of two branches, 256 rows: 9.8 against 10.7), 80 to 104 tiles 1.04 (333
+    // rows: 11.5 against 10.8), 128 tiles 1.06, 160 to 208 1.2, 320 1.4.
+    if (tiles(32) <= 64) return bk ? launch_fwd<T16x16>(epi, nb, g, gm, s) : launch_adj<T16x16>(epi, g, gm, s);
     return bk ? launch_fwd<T32x32>(epi, nb, g, gm, s) : launch_adj<T32x32>(epi, g, gm, s);
   }
   // Enough tiles to fill the card several times: larger ones.  16384 rows of
