@@ -367,7 +367,7 @@ edpc_status edpc_model_step(edpc_model* mh, const uint8_t* d_ctx, const uint8_t*
     out.keep_fdm_grad = (flags & EDPC_STEP_KEEP_FDM_GRAD) != 0 && !out.update;
     if (out.keep_fdm_grad && !m.dUkeep) m.dUkeep = m.mem.take<float>(m.n_slots * (size_t)m.L * m.L);
     if (out.keep_fdm_grad)  // slots outside this call get a zero gradient
-      hip_check(hipMemsetAsync(m.dUkeep, 0, m.n_slots * (size_t)m.L * m.L * sizeof(float), s), "memset");
+      k_zero(m.dUkeep, m.n_slots * (size_t)m.L * m.L, s);
     const uint32_t tau = out.update ? (uint32_t)(m.tau + 1) : (uint32_t)(m.tau > 0 ? m.tau : 1);
     if (rows <= (size_t)kInlineSlots && on_this_device(d_ctx) && (!d_target || on_this_device(d_target))) {
       InlineSlots in;

@@ -195,6 +195,9 @@ void k_init_shared(const InitTensor* t, int n, size_t total, uint64_t seed, floa
                    float* v, float* g, bf16_t* p16, hipStream_t s);
 void k_init_streams(float* u, float* m, float* v, size_t n, uint64_t seed, uint32_t tid, float bound,
                     hipStream_t s);
+// A kernel and not a memset: callers may capture it, and captured memsets have given
+// wrong results on replays after the first.  n a multiple of 4.
+void k_zero(float* dst, size_t n, hipStream_t s);
 void k_to_bf16(const float* src, bf16_t* dst, size_t n, hipStream_t s);
 
 // Coder lanes.

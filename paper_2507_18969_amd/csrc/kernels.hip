@@ -936,6 +936,17 @@ void k_init_streams(float* u, float* m, float* v, size_t n, uint64_t seed, uint3
                      seed + ((uint64_t)tid << 40), bound);
 }
 
+__global__ void __launch_bounds__(256) zero_kernel(float* __restrict__ dst, size_t n) {
+  for (size_t j = 4 * ((size_t)blockIdx.x * 256 + threadIdx.x); j < n; j += 4 * (size_t)gridDim.x * 256)
+    *(float4*)(dst + j) = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
+void k_zero(float* dst, size_t n, hipStream_t s) {
+  const size_t blocks = (n / 4 + 255) / 256;
+  hipLaunchKernelGGL(zero_kernel, dim3((unsigned)std::min<size_t>(std::max<size_t>(blocks, 1), 65536)), dim3(256), 0, s,
+                     dst, n);
+}
+
 __global__ void to_bf16_kernel(const float* src, bf16_t* dst, size_t n) {
   const size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j < n) dst[j] = f2bf(src[j]);
