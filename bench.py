@@ -41,7 +41,8 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 157.3}  # dense MFMA peaks of MI355X
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_mid_1024x64KiB.txt")
 KERNEL_TIMING_STEPS = 64
 KERNEL_SOURCES = ["fused.hip", "fused.h", "kernels.hip", "kernels.h", "common.h", "head_row.h",
-                  "rangecoder.h", "adam.h", "gemm.h", "gemm.hip"]
+                  "rangecoder.h", "adam.h", "gemm.h", "gemm.hip", "wgrad_adam.hip", "grad_sums.h",
+                  "ln_row.h"]
 
 
 def log(msg):
@@ -175,11 +176,15 @@ TILE_NAMES = ("32x32", "64x32", "32x64", "64x64", "128x64", "64x128", "128x128",
               "w128x128", "w256x128", "w128x256", "w256x256")
 
 
-def kernel_tiles(kernel_id):
+def kernel_tiles(kernel_id, precision):
     """Tile shape per product class of a container's kernel configuration id
-    (4 bits per product slot, slots in GEMM_CLASSES order)."""
-    return {c: TILE_NAMES[(kernel_id >> (4 * i)) & 15] if ((kernel_id >> (4 * i)) & 15) < len(TILE_NAMES)
-            else "?" for i, c in enumerate(GEMM_CLASSES)}
+    (4 bits per product slot, slots in GEMM_CLASSES order).  FP32 products but
+    the weight gradients: an id is a matrix instruction, the tile goes by size."""
+    def name(c, t):
+        if precision == "fp32" and c != "gemm_weight_grads":
+            return "mfma 16x16x4" if t < 3 else "mfma 32x32x2"
+        return TILE_NAMES[t] if t < len(TILE_NAMES) else "?"
+    return {c: name(c, (kernel_id >> (4 * i)) & 15) for i, c in enumerate(GEMM_CLASSES)}
 
 
 def copy_rate(torch, nbytes=4 << 30, reps=3):
@@ -267,7 +272,7 @@ def large_workload(torch, E, precisions, warmup=8, kernel_steps=8, steps=24):
                                              for k, v in kern.items() if v[1]},
                      "roofline_fdm_bwd_adam": fdm_roofline(w, kern, rows, stored=False),
                      "roofline_gemm": gemm_roofline(w, kern, rows, prec, kernel_steps),
-                     "tiles": kernel_tiles(r["kernel_id"])}
+                     "tiles": kernel_tiles(r["kernel_id"], prec)}
         log(f"large {prec}: {out[prec]['encode_MBps']} / {out[prec]['decode_MBps']} MB/s")
     if "bf16" in out and "fp32" in out:
         out["bf16_over_fp32_encode"] = round(out["bf16"]["encode_MBps"] / out["fp32"]["encode_MBps"], 3)

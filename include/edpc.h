@@ -217,7 +217,9 @@ void edpc_session_destroy(edpc_session* s);
  * with a HIP event recorded before and after every kernel launch on the
  * session's stream, then synchronises: h_ms[c] receives the summed kernel
  * milliseconds and h_launches[c] the launch count of kernel class c, for
- * c < EDPC_KCLASS_COUNT.  The class names come from edpc_kclass_name. */
+ * c < EDPC_KCLASS_COUNT.  The class names come from edpc_kclass_name; classes
+ * without a launch of their own ("step_schedule" and "gather", whose work the
+ * step's first kernel does) stay at zero. */
 #define EDPC_KCLASS_COUNT 24
 edpc_status edpc_session_time_kernels(edpc_session* s, uint64_t n_steps, float* h_ms,
                                       uint32_t* h_launches);

@@ -76,10 +76,13 @@ struct Session {
   Schedule sched;
 
   // captured step windows: grid-row bucket -> executable graph of graph_steps
-  // steps, where a bucket lasts kGraphMinSteps steps: a capture costs 1 to 3 ms
-  // and saves 7 us a step of 32 launches, and nothing of a step whose kernels
-  // take longer than their launches.  8 streams, FP32: 74 steps 8.7 ms launched
-  // directly, 10.2 captured; 304 steps 38.0 against 37.1.
+  // steps, where a bucket lasts kGraphMinSteps steps.  A capture costs 2 to 3 us a
+  // launch of its 32 steps and saves 1 to 7 us a step where 8 streams leave the
+  // kernels shorter than their launches, and nothing where they are longer.  Captured
+  // against direct, ms: 8 streams, BF16 (6 launches a step) 400 steps 19.5 and 19.8, FP32
+  // (8 launches) 400 steps 34.6 and 34.7, 1000 steps 87.4 and 88.6, BF16 layer by layer
+  // of 4 blocks (38 launches) 400 steps 55.2 and 56.8, 1000 steps 138 and 145; but 300
+  // streams, FP32 of 8 launches, 400 steps 40.8 and 40.1, of 36 launches 93.4 and 90.5.
   int graph_steps = 0;
   std::map<int, hipGraphExec_t> graphs;
   hipStream_t cap = nullptr;  // private non-blocking stream used only for capture

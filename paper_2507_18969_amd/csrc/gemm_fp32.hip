@@ -332,7 +332,8 @@ __global__ void __launch_bounds__(kF32Threads) gemm_fp32_kernel(GemmArgs g) {
 // the column sums, which are independent of the tiles and would leave most of the
 // chip idle in launches of their own (8 streams of a small model: 14.3 us
 // in three launches, 5.3 in this one; 333 rows of a mid one 42.3 and 20.9; 1024
-// rows 67.7 and 47.7).
+// rows 67.7 and 47.7).  Its price: every tile's kernel has the registers of the widest
+// embedding gradient, two waves a SIMD where the 32 x 32 tile alone would have six.
 template <class T>
 __global__ void __launch_bounds__(kF32Threads) wgrad_fp32_kernel(const WgradProblem* __restrict__ probs,
                                                                  int n_probs, int tiles, int emb_blocks,

@@ -258,8 +258,9 @@ void k_fdm_fwd(const StepState* st, const float* x1, const float* U, const uint3
 //   dx'_s = U_s dy_s (with U before the update), dU_s = x'_s (x) dy_s.
 // Bound by memory: 24 bytes an element of U_s.  The rows of U_s are independent,
 // so `split` workgroups share a slot; one workgroup a slot leaves the last
-// round of workgroups short and too few loads in flight.
-// (FIGURES)
+// round of workgroups short and too few loads in flight (slots of 128 x 128, one and
+// four workgroups: 8 slots 17.2 and 6.8 us, 300 slots 27.7 and 21.9, 700 slots 46.2 and
+// 43.4, 1024 slots 65.2 and 66.2, 3000 slots 179 and 173).
 template <int CACHE>
 __global__ void __launch_bounds__(256) fdm_bwd_kernel(
     const StepState* __restrict__ st, const float* __restrict__ x1, const float* __restrict__ dy,

@@ -59,7 +59,9 @@ struct TensorInfo {
   float bound;   // RNG bound or constant value
 };
 
-// Kernel classes for per-kernel timing: the product slots, then the rest.
+// Kernel classes for per-kernel timing: the product slots, then the rest.  The first
+// two have no launch of their own (the embedding's forms the step state and gathers
+// the contexts): they keep their numbers and stay at zero.
 enum KClass : int {
   KC_SCHEDULE = PS_COUNT,
   KC_GATHER,
