@@ -71,7 +71,7 @@ __global__ void __launch_bounds__(256) embed_kernel(const StepState* __restrict_
                                                     const uint8_t* __restrict__ ctx,
                                                     const float* __restrict__ emb, int C, int E, int per, int n,
                                                     float* __restrict__ x32, bf16_t* __restrict__ x16) {
-  const int i = threadIdx.x / n, r = blockIdx.x * per + i;
+  const int i = per > 1 ? threadIdx.x / n : 0, r = blockIdx.x * per + i;
   if (i >= per || r >= st->rows) return;
   embed_row(ctx + (size_t)r * C, emb, C * E, E, x32, x16, r, threadIdx.x - i * n, n);
 }
