@@ -48,11 +48,11 @@ void k_step_explicit(StepState* st, int rows, uint32_t tau, float beta1, float b
 // ---------------------------------------------------------------------------
 // Context window gather and byte embedding
 // ---------------------------------------------------------------------------
-// X[r][c E + e] = Emb[byte c of row r's context][e]; thread t of n.
+// X[r][c E + e] = Emb[byte c of row r's context][e], features f, f + step, ..
 __device__ __forceinline__ void embed_row(const uint8_t* bytes, const float* __restrict__ emb, int F, int E,
-                                          float* __restrict__ x32, bf16_t* __restrict__ x16, size_t r, int t,
-                                          int n) {
-  for (int f = 4 * t; f < F; f += 4 * n) {
+                                          float* __restrict__ x32, bf16_t* __restrict__ x16, size_t r, int f,
+                                          int step) {
+  for (; f < F; f += step) {
     const int c = f / E, e = f - c * E;
     const float4 val = *(const float4*)(emb + bytes[c] * E + e);
     if (x32) *(float4*)(x32 + r * F + f) = val;
@@ -64,23 +64,26 @@ __device__ __forceinline__ void embed_row(const uint8_t* bytes, const float* __r
 // A workgroup takes `per` rows with n threads each: one row, or from 2048 rows on as
 // many as fit (below 1024 features one row leaves threads idle, which costs nothing
 // while there are CUs to spare: a BF16 prediction of 100000 rows of 64 features 279 us,
-// 259 so, of 256 features 433 and 418; 7 rows of 256 44.9 us, 45.1 together.  A thread
-// per 4 features over all rows is no faster and takes 163 us against 160 at 8000 rows
-// of 4096).
+// 259 so, of 256 features 433 and 418; 7 rows of 256 44.9 us, 45.1 together).  Up to 512
+// rows, wide ones are shared out over workgroups of 1024 features (blockIdx.y): one would
+// wait for its rounds of loads in turn (5 rows of 16384 features 145.4 us a prediction,
+// 139.8 so; 3000 rows 347 and 357).
 __global__ void __launch_bounds__(256) embed_kernel(const StepState* __restrict__ st,
                                                     const uint8_t* __restrict__ ctx,
                                                     const float* __restrict__ emb, int C, int E, int per, int n,
                                                     float* __restrict__ x32, bf16_t* __restrict__ x16) {
   const int i = per > 1 ? threadIdx.x / n : 0, r = blockIdx.x * per + i;
   if (i >= per || r >= st->rows) return;
-  embed_row(ctx + (size_t)r * C, emb, C * E, E, x32, x16, r, threadIdx.x - i * n, n);
+  embed_row(ctx + (size_t)r * C, emb, C * E, E, x32, x16, r, 1024 * blockIdx.y + 4 * (threadIdx.x - i * n),
+            1024 * gridDim.y);
 }
 
 void k_embed(const StepState* st, const uint8_t* ctx, const float* emb, int C, int E, float* x32,
              bf16_t* x16, int max_rows, hipStream_t s) {
   const int n = max_rows < 2048 ? 256 : std::min(256, C * E / 4), per = 256 / n;
-  hipLaunchKernelGGL(embed_kernel, dim3(blocks_for(max_rows, per)), dim3(256), 0, s, st, ctx, emb, C, E, per, n,
-                     x32, x16);
+  const unsigned share = max_rows <= 512 ? blocks_for(C * E, 1024) : 1;
+  hipLaunchKernelGGL(embed_kernel, dim3(blocks_for(max_rows, per), share), dim3(256), 0, s, st, ctx, emb, C, E, per,
+                     n, x32, x16);
 }
 
 // First launch of a coding step of the layer-by-layer sequence: the step state
@@ -111,7 +114,7 @@ __global__ void __launch_bounds__(256) embed_streams_kernel(StepState* st, Sched
     }
     if (!decoding && c == 0) tgt[r] = io.src[io_at(io, o, (uint64_t)step)];
     __syncthreads();
-    embed_row(bytes, emb, C * E, E, x32, x16, r, threadIdx.x, 256);
+    embed_row(bytes, emb, C * E, E, x32, x16, r, 4 * threadIdx.x, 1024);
   }
   if (r == 0) {
     const int rows = active_rows(sc, step);

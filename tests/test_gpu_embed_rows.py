@@ -52,3 +52,21 @@ def test_rows_among_others(E, context, embed, precision):
         few = torch.empty(7, 256, device="cuda")
         m.edpc_model_step(ctx[a:a + 7].clone(), None, np.arange(a, a + 7), probs=few)
         assert torch.equal(few, probs[a:a + 7]), a
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("context,embed", [(64, 16), (68, 16), (132, 16), (64, 64), (256, 64)])
+def test_wide_rows(E, context, embed, precision):
+    """Wide rows: shared out over workgroups up to 512 rows, whole past that."""
+    cfg = dict(context=context, embed=embed, latent=16, blocks=0, hidden=16, branches=1, lr=1e-3, beta1=0.9,
+               beta2=0.999, eps=1e-8, seed=5)
+    rows = 513
+    banner(f"embedding {context} x {embed} {precision}, wide rows")
+    m = E.Model(lib_cfg(E, cfg, precision), rows, rows)
+    ctx = torch.as_tensor(np.random.RandomState(4).randint(0, 256, (rows, context)).astype(np.uint8)).to("cuda")
+    whole = torch.empty(rows, 256, device="cuda")
+    m.edpc_model_step(ctx, None, np.arange(rows), probs=whole)
+    for a, n in ((0, 1), (500, 13), (0, 512)):
+        part = torch.empty(n, 256, device="cuda")
+        m.edpc_model_step(ctx[a:a + n].clone(), None, np.arange(a, a + n), probs=part)
+        assert torch.equal(part, whole[a:a + n]), (a, n)
