@@ -629,19 +629,22 @@ def fused_roofline(w, kern, rows, precision):
             "algorithmic_flops_per_launch": flops, "avg_launch_us": round(per_launch_s * 1e6, 2)}
 
 
-# Per-CU limit on L2 reads in flight and the mean L2 read latency the
-# row-block kernel sees (rocprofv3 TCP_TCC_READ_REQ(_LATENCY) counters of the
-# 1024-stream BF16 step): the rate at which one CU can stream operands from L2.
+# Per-CU limit on L2 reads in flight, and the mean latency of the row blocks' own
+# L2 reads (rocprofv3 TCP_TCC_READ_REQ(_LATENCY) counters of the 1024-stream BF16
+# step; the reads of the work-groups that fetch weights ahead are taken off, by
+# runs of 16 and 300 rows): the rate at which one CU could stream operands from L2.
 CU_L2_READS_IN_FLIGHT = 64
-CU_L2_READ_LATENCY_CYCLES = 290
+CU_L2_READ_LATENCY_CYCLES = 196
 CLOCK_GHZ = 2.4
 
 
 def fused_stream_bound(w, kern, rows):
-    """The bound the row-block kernel actually meets: every workgroup (one
-    per CU, 16 rows) streams each BF16 weight of its products twice (forward
-    and adjoint orientation) from L2, and a CU can keep only so many L2 reads
-    in flight.  Achieved = those bytes over the launch time, per CU clock."""
+    """The row-block kernel against the nearest limit of its data path: every
+    workgroup (one per CU, 16 rows) streams each BF16 weight of its products twice
+    (forward and adjoint orientation) from L2, and a CU can keep only so many L2
+    reads in flight.  Achieved = those bytes over the launch time, per CU clock.  A
+    fraction well below 1 means that the kernel waits for its chain of stages, not
+    for this limit."""
     if w.precision != "bf16" or "fused_rowblock_step" not in kern:
         return None
     ms, launches = kern["fused_rowblock_step"]

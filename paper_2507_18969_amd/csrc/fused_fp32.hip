@@ -60,9 +60,11 @@ __device__ __forceinline__ int frag_at(int m, int k) {
   return (k >> 4) * 256 + (k & 3) * 64 + 4 * m + ((k >> 2) & 3);
 }
 
-// A CU has about a hundred requests to L2 in flight, whatever their size, and that
-// bounds the kernel: weights are read as whole 128-byte lines (64-byte pieces,
-// without the detours below: 11 to 16 bytes a clock instead of 27).
+// Weights are read as whole 128-byte lines: an L2 request takes as long whatever its
+// size, and a CU has at most about 64 in flight (products on 64-byte pieces, without
+// the detours below, got 11 to 16 bytes a clock, on lines 27; over the whole kernel,
+// epilogues included, 22 to 36 requests are in flight: 18 thousand of 186 clocks at
+// 1024 rows, of 295 at 16).
 //
 // One wave's 16 columns of [16, K] x W^T, W[n][k], NB times (the matrices of a gated
 // product, or columns further on), with D groups of 32 k in flight.  A load takes 8 rows of 32 k; the
