@@ -434,8 +434,14 @@ hipError_t launch_gemm_fp32(int tile, bool ak, bool bk, EpiKind epi, int nb, con
     // tile, with half the operands a product, is the better one.  All products of
     // steps of 16 to 640 rows, time of 16 x 16 over 32 x 32: 16 to 64 tiles 0.94 (gated
     // K 512 of two branches, 256 rows: 9.8 against 10.7), 80 to 104 tiles 1.04 (333
-    // rows: 11.5 against 10.8), 128 tiles 1.06, 160 to 208 1.2, 320 1.4.
-    if (tiles(32) <= 64) return bk ? launch_fwd<T16x16>(epi, nb, g, gm, s) : launch_adj<T16x16>(epi, g, gm, s);
+    // rows: 11.5 against 10.8), 128 tiles 1.06, 160 to 208 1.2, 320 1.4.  Two kinds of
+    // product hold out longer: gated ones of a long K (K 1024: 80 and 96 tiles 0.96, the
+    // adjoint 0.92, 128 tiles 1.01 and 0.94, 176 tiles 1.17), and plain forward ones of few
+    // columns (K 512 and 1024, 128 or 256 columns: 80 to 104 tiles 0.95, 128 tiles 0.99 to
+    // 1.02, 160 tiles 1.13).
+    const bool later = epi == EPI_STORE ? bk && g.K >= 512 && g.N <= 256 : g.K >= 1024;
+    if (tiles(32) <= (later ? 127 : 64))
+      return bk ? launch_fwd<T16x16>(epi, nb, g, gm, s) : launch_adj<T16x16>(epi, g, gm, s);
     return bk ? launch_fwd<T32x32>(epi, nb, g, gm, s) : launch_adj<T32x32>(epi, g, gm, s);
   }
   // Enough tiles to fill the card several times: larger ones.  16384 rows of

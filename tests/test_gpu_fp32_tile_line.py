@@ -1,6 +1,6 @@
 """FP32 products on both sides of the line between 16 x 16 and 32 x 32 tiles (64 tiles
-of 32 x 32: 256 rows for 256 outputs, 512 for 128): a row's results are the same bits
-on either."""
+of 32 x 32: 256 rows for 256 outputs, 512 for 128; for a K of 512 and 1024 features 127
+tiles): a row's results are the same bits on either."""
 
 import numpy as np
 import pytest
@@ -22,15 +22,16 @@ def E():
     return E
 
 
+@pytest.mark.parametrize("context", [16, 32, 64])
 @pytest.mark.parametrize("branches", [1, 2, 3])
-def test_line(E, branches):
+def test_line(E, branches, context):
     rng = np.random.RandomState(branches)
-    ctx = torch.as_tensor(rng.randint(0, 256, (1024, 16)).astype(np.uint8)).to("cuda")
+    ctx = torch.as_tensor(rng.randint(0, 256, (1024, context)).astype(np.uint8)).to("cuda")
     tgt = torch.as_tensor(rng.randint(0, 256, 1024).astype(np.uint8)).to("cuda")
-    m = E.Model(lib_cfg(E, dict(MODEL, branches=branches), layerwise=True), 1024, 1024)
+    m = E.Model(lib_cfg(E, dict(MODEL, branches=branches, context=context), layerwise=True), 1024, 1024)
     got = {}
-    for rows in (64, 256, 257, 512, 513, 1024):
-        banner(f"FP32 tile line, {branches} branches, {rows} rows")
+    for rows in (64, 256, 257, 480, 512, 513, 1024):
+        banner(f"FP32 tile line, context {context}, {branches} branches, {rows} rows")
         p = torch.empty(rows, 256, device="cuda")
         m.edpc_model_step(ctx[:rows], tgt[:rows], np.arange(rows), probs=p,
                           flags=E.EDPC_STEP_BACKWARD | E.EDPC_STEP_KEEP_FDM_GRAD)
